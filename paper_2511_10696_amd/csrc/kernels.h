@@ -63,8 +63,8 @@ struct BwdParams {
 
 hipError_t launch_index_set(int n, int k, int pi, bool causal, int32_t *idx, hipStream_t stream);
 
-// Reference-style fp32 kernels: one wavefront per query, W_t visited entry by
-// entry with an online softmax.  Correctness path for float32 data.
+// float32: the forward on MFMA tiles of 16 queries; decode one wavefront per
+// (sequence, head), W_t visited entry by entry with an online softmax.
 hipError_t launch_forward_f32(const FwdParams &p, hipStream_t stream);
 hipError_t launch_decode_f32(const DecodeParams &p, hipStream_t stream);
 
@@ -74,14 +74,17 @@ hipError_t launch_forward_bf16(const FwdParams &p, hipStream_t stream);
 // bf16 decode step, working set split across wavefronts (D = 64 or 128).
 hipError_t launch_decode_bf16(const DecodeParams &p, hipStream_t stream);
 
-// Backward: the row terms <dL/dy_t, y_t>, a query pass (dq, dgate) and a
-// key pass (dk, dv).
+// Backward: a query pass (dq, dgate, row terms <dL/dy_t, y_t>) and a key pass
+// (dk, dv); picks the kernels by dtype and window.
 hipError_t launch_backward(const BwdParams &p, hipStream_t stream);
 
 // out[h] = sum over b and t of dgate[b][h][t] (fixed order, fp64 sums).
 hipError_t launch_gate_grad_per_head(int B, int H, int N, const float *dgate, float *out, hipStream_t stream);
 
-// MFMA query pass (dq, dgate) for bf16 inputs; needs the row terms.
+// Both passes for float32 data.
+hipError_t launch_backward_f32(const BwdParams &p, hipStream_t stream);
+
+// MFMA query pass (dq, dgate, row terms) for bf16 inputs.
 hipError_t launch_backward_q_bf16(const BwdParams &p, hipStream_t stream);
 
 // MFMA key pass (dk, dv) for bf16 inputs; needs the row terms.
