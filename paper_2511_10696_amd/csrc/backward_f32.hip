@@ -99,7 +99,7 @@ __global__ __launch_bounds__(NT, D == 64 && !SPLIT ? 4 : 2) void backward_q_f32_
     {
         RowFrag<D> y;
         load_row<D>(y, (const float *)bp.out + obase + tq * bp.osn, g);
-        r_t = col_sum(dot_lane<D>(o, y));
+        r_t = (float)col_sum(dot_lane<D>(o, y));
     }
     Acc<D> dq;
 #pragma unroll

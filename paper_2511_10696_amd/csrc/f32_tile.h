@@ -65,34 +65,34 @@ __device__ inline void load_cols(ColFrag<D> &f, RowPtr row, int c, int g) {
 }
 
 // Scores of the block's 16 rows with the tile's 16 columns: slot r of lane
-// (c, g) is <row 4 g + r, column c>.  Two chains: the instruction's latency
-// is longer than its issue, and half the summands round together.
+// (c, g) is <row 4 g + r, column c>.  Four chains: the instruction's latency
+// is longer than its issue, and a quarter of the summands round together.
 template <int D>
 __device__ inline f32x4 dot_rows(const RowFrag<D> &rows, const RowFrag<D> &cols) {
-    f32x4 s0 = {}, s1 = {};
+    f32x4 sum[4] = {};
 #pragma unroll
-    for (int s = 0; s < D / 16; s += 2) {
+    for (int s = 0; s < D / 16; ++s)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(rows.x[s][e], cols.x[s][e], s0, 0, 0, 0);
-            s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(rows.x[s + 1][e], cols.x[s + 1][e], s1, 0, 0, 0);
-        }
-    }
-    return s0 + s1;
+        for (int e = 0; e < 4; ++e)
+            sum[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(rows.x[s][e], cols.x[s][e], sum[e], 0, 0, 0);
+    return (sum[0] + sum[1]) + (sum[2] + sum[3]);
 }
 
+// This lane's part of <a, b>, summed in 64 bits: it is formed once per
+// column, and the gate gradient's sum of ddelta nearly cancels.
 template <int D>
-__device__ inline float dot_lane(const RowFrag<D> &a, const RowFrag<D> &b) {
-    float s = 0.0f;
+__device__ inline double dot_lane(const RowFrag<D> &a, const RowFrag<D> &b) {
+    double s = 0.0;
 #pragma unroll
     for (int i = 0; i < D / 16; ++i)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) s = __builtin_fmaf(a.x[i][e], b.x[i][e], s);
+        for (int e = 0; e < 4; ++e) s = __builtin_fma((double)a.x[i][e], (double)b.x[i][e], s);
     return s;
 }
 
 // Sum and maximum over the four lanes of a column.
-__device__ inline float col_sum(float x) {
+template <typename T>
+__device__ inline T col_sum(T x) {
     x += __shfl_xor(x, 16);
     return x + __shfl_xor(x, 32);
 }
