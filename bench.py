@@ -509,7 +509,7 @@ def main():
         per = sorted(ev[i].elapsed_time(ev[i + 1]) for i in range(nsteps))
         dkeys, dbytes = decode_algorithmic(dcfg, dcfg.cache_len)
         ddigest = source_digest([os.path.join(ROOT, "paper_2511_10696_amd", "csrc", f)
-                                 for f in ("decode_bf16.hip", "pi_common.h", "kernels.h")])
+                                 for f in ("decode.hip", "pi_common.h", "kernels.h")])
         dtraffic = measured_traffic(ddigest, DECODE_TRAFFIC)
         dcounters = measured_counters(ddigest, DECODE_TRAFFIC, dms / 1e3)
         dgbs = dbytes / (dms / 1e3) / 1e9
@@ -518,7 +518,7 @@ def main():
                   "us_per_step_p50": round(per[len(per) // 2] * 1e3, 2),
                   "us_per_step_p99": round(per[min(len(per) - 1, (99 * len(per)) // 100)] * 1e3, 2),
                   "queries_per_s": round(dcfg.S / (dms / 1e3), 1),
-                  "roofline": {"bound": "hbm", "kernel": "decode_bf16_kernel<128>",
+                  "roofline": {"bound": "hbm", "kernel": "decode_kernel<bf16, 128>",
                                "achieved": round(dgbs, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                "frac": round(dgbs / HBM_PEAK_GBS, 4), "bytes_per_step": dbytes,
                                "traffic": dtraffic, **dcounters}}

@@ -301,7 +301,7 @@ int pi_attn_decode_step(int32_t dtype, int32_t S, int32_t H, int32_t D, int32_t 
     p.clamp = logit_clamp > 0.0f ? logit_clamp : 0.0f;
     p.out = out; p.lse = lse;
     const hipStream_t st = (hipStream_t)stream;
-    return from_hip(dtype == PI_ATTN_BF16 ? launch_decode_bf16(p, st) : launch_decode_f32(p, st));
+    return from_hip(launch_decode(p, dtype == PI_ATTN_BF16, st));
 }
 
 int pi_attn_forward_shard(int32_t dtype, int32_t B, int32_t H, int32_t D, int32_t k, int32_t pi, int32_t causal,

@@ -1,11 +1,11 @@
-// attn_f32.hip -- float32 forward (MFMA tiles) and decode.
+// attn_f32.hip -- float32 forward.
 //
-// Forward: v_mfma_f32_16x16x4f32 (float32 products and sums), tiles and
-// layouts as in f32_tile.h.  A wavefront owns 16 queries; per block of 16
-// keys S^T = K Q^T lands with lane (c, g) holding the scores of query c for
-// keys 4 g + r, the softmax reductions are in-lane plus two exchanges, and
-// O^T += V^T P^T takes P^T straight from the score registers.  A partner run
-// is one more block of which only the diagonal is valid.
+// v_mfma_f32_16x16x4f32 (float32 products and sums), tiles and layouts as in
+// f32_tile.h.  A wavefront owns 16 queries; per block of 16 keys S^T = K Q^T
+// lands with lane (c, g) holding the scores of query c for keys 4 g + r, the
+// softmax reductions are in-lane plus two exchanges, and O^T += V^T P^T takes
+// P^T straight from the score registers.  A partner run is one more block of
+// which only the diagonal is valid.
 //
 // What bounds it: the float32 matrix rate (a block of 16 x 16 entries costs
 // 2 x D / 4 instructions of 32 clocks, used by k + 1 of k + 16 keys) at large
@@ -170,93 +170,6 @@ __global__ __launch_bounds__(NT, D == 64 && !SPLIT ? 4 : 2) void forward_f32_ker
     }
 }
 
-// ---- decode: one wavefront per (sequence, head) --------------------------------
-// Lane l holds elements l, l + 64, ... of the D-vector; the working set is
-// visited entry by entry with an online softmax in the log2 domain.
-__device__ inline float wave_sum(float x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-    return x;
-}
-
-template <int D>
-struct OnlineRow {
-    static constexpr int E = D / 64;
-    float q[E];
-    float acc[E];
-    float m = -INFINITY;   // running max, log2 domain
-    float l = 0.0f;        // running sum of exp2(s - m)
-
-    // One working-set entry: key row kj, value row vj, fused bias (natural log).
-    __device__ inline void visit(const float *kj, const float *vj, float bias, float scale, float clamp, int lane) {
-        float part = 0.0f;
-#pragma unroll
-        for (int e = 0; e < E; ++e) part += q[e] * kj[lane + 64 * e];
-        float delta = wave_sum(part) * scale + bias;
-        if (clamp > 0.0f) delta = fminf(fmaxf(delta, -clamp), clamp);
-        float s = delta * kLog2e;
-        float mn = fmaxf(m, s);
-        float c = __builtin_amdgcn_exp2f(m - mn);   // m = -inf -> 0
-        float pr = __builtin_amdgcn_exp2f(s - mn);
-        l = l * c + pr;
-#pragma unroll
-        for (int e = 0; e < E; ++e) acc[e] = acc[e] * c + pr * vj[lane + 64 * e];
-        m = mn;
-    }
-};
-
-template <int D>
-__global__ __launch_bounds__(256) void decode_f32_kernel(DecodeParams p) {
-    const int lane = threadIdx.x & 63;
-    const int64_t sh = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (sh >= (int64_t)p.S * p.H) return;
-    const int s = (int)(sh / p.H), h = (int)(sh % p.H);
-    const int t = p.len_in[s];
-    float *out = (float *)p.out;
-    if (t < 0 || t >= p.cap) {
-        for (int e = lane; e < D; e += 64) out[sh * D + e] = NAN;
-        if (lane == 0) {
-            if (p.lse) p.lse[sh] = NAN;
-            if (p.len_out && h == 0) p.len_out[s] = t;
-        }
-        return;
-    }
-    const float *qn = (const float *)p.q_new + sh * D;
-    const float *kn = (const float *)p.k_new + sh * D;
-    const float *vn = (const float *)p.v_new + sh * D;
-    float *kc = (float *)p.k_cache + sh * (int64_t)p.cap * D;
-    float *vc = (float *)p.v_cache + sh * (int64_t)p.cap * D;
-
-    OnlineRow<D> st;
-#pragma unroll
-    for (int e = 0; e < OnlineRow<D>::E; ++e) {
-        st.q[e] = qn[lane + 64 * e];
-        st.acc[e] = 0.0f;
-    }
-    const bool exact = p.clamp > 0.0f;
-    const FusionBias fb = fusion_bias(p.gate[s * p.gss + h * p.gsh], exact);
-
-    const int jp = partner_of(t, p.k, p.pi);
-    if (jp >= 0) st.visit(kc + (int64_t)jp * D, vc + (int64_t)jp * D, fb.partner, p.scale, p.clamp, lane);
-    for (int j = window_lo(t, p.k); j < t; ++j)
-        st.visit(kc + (int64_t)j * D, vc + (int64_t)j * D, fb.local, p.scale, p.clamp, lane);
-    st.visit(kn, vn, fb.local, p.scale, p.clamp, lane);   // self: the new row t
-
-    // Append the new key/value as cache row t (rows read above are all < t).
-#pragma unroll
-    for (int e = 0; e < OnlineRow<D>::E; ++e) {
-        kc[(int64_t)t * D + lane + 64 * e] = kn[lane + 64 * e];
-        vc[(int64_t)t * D + lane + 64 * e] = vn[lane + 64 * e];
-    }
-    const float inv = 1.0f / st.l;
-#pragma unroll
-    for (int e = 0; e < OnlineRow<D>::E; ++e) out[sh * D + lane + 64 * e] = st.acc[e] * inv;
-    if (lane == 0) {
-        if (p.lse) p.lse[sh] = (st.m + __log2f(st.l)) * kLn2 + fb.lse_shift;
-        if (p.len_out && h == 0) p.len_out[s] = t + 1;
-    }
-}
-
 template <int D>
 hipError_t launch_fwd(const FwdParams &p, hipStream_t stream) {
     const int n_qt = (p.N + TILE - 1) / TILE;
@@ -272,14 +185,6 @@ hipError_t launch_fwd(const FwdParams &p, hipStream_t stream) {
 hipError_t launch_forward_f32(const FwdParams &p, hipStream_t stream) {
     if ((int64_t)p.B * p.H * p.N == 0) return hipSuccess;
     return p.D == 64 ? launch_fwd<64>(p, stream) : launch_fwd<128>(p, stream);
-}
-
-hipError_t launch_decode_f32(const DecodeParams &p, hipStream_t stream) {
-    int64_t n = (int64_t)p.S * p.H;
-    if (n == 0) return hipSuccess;
-    dim3 grid((unsigned)((n + 3) / 4)), block(256);
-    if (p.D == 64) return launch_kernel(decode_f32_kernel<64>, grid, block, stream, p);
-    return launch_kernel(decode_f32_kernel<128>, grid, block, stream, p);
 }
 
 }  // namespace pi_attn

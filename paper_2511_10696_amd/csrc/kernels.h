@@ -63,16 +63,14 @@ struct BwdParams {
 
 hipError_t launch_index_set(int n, int k, int pi, bool causal, int32_t *idx, hipStream_t stream);
 
-// float32: the forward on MFMA tiles of 16 queries; decode one wavefront per
-// (sequence, head), W_t visited entry by entry with an online softmax.
+// float32 forward on MFMA tiles of 16 queries (D = 64 or 128).
 hipError_t launch_forward_f32(const FwdParams &p, hipStream_t stream);
-hipError_t launch_decode_f32(const DecodeParams &p, hipStream_t stream);
 
 // bf16 banded MFMA forward (D = 64 or 128).
 hipError_t launch_forward_bf16(const FwdParams &p, hipStream_t stream);
 
-// bf16 decode step, working set split across wavefronts (D = 64 or 128).
-hipError_t launch_decode_bf16(const DecodeParams &p, hipStream_t stream);
+// Decode step, working set split across wavefronts (D = 64 or 128).
+hipError_t launch_decode(const DecodeParams &p, bool bf16, hipStream_t stream);
 
 // Backward: a query pass (dq, dgate, row terms <dL/dy_t, y_t>) and a key pass
 // (dk, dv); picks the kernels by dtype and window.
