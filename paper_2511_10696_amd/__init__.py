@@ -5,6 +5,11 @@ HIP stream) into the C ABI declared in ``include/pi_attn.h``; every step of
 the operator runs in the library's HIP kernels.  There is no fallback: if the
 library is missing or the tensors are not on the GPU, the calls raise.
 
+The forward, the gated forward, the backward and the decode step marshal
+their plain calls in native code (``csrc/binding.cpp``), which returns None
+for anything unusual or wrong before it enqueues anything; the Python code
+below it then serves the call, or says what is wrong with it.
+
 Entry points (same names as the C ABI; ``causal=False`` selects the
 bidirectional mode, window |j - t| <= k and partners t -/+ pi):
     pi_attn_index_set(n, k, pi, causal=True)                  -> int32 [n, m] (device)
@@ -26,6 +31,7 @@ __all__ = ["pi_attn_index_set", "pi_attn_forward", "pi_attn_forward_gated", "pi_
            "pi_attn_strerror", "library", "LIB_PATH", "EXPORTED_SYMBOLS", "PiAttnError"]
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libpi_attn.so")
+BINDING_PATH = os.path.join(os.path.dirname(LIB_PATH), "_binding.so")
 EXPORTED_SYMBOLS = ("pi_attn_strerror", "pi_attn_ws_width", "pi_attn_default_scale", "pi_attn_index_set",
                     "pi_attn_forward", "pi_attn_forward_gated", "pi_attn_decode_step", "pi_attn_backward",
                     "pi_attn_gate_grad_per_head", "pi_attn_forward_shard", "pi_attn_backward_shard_q",
@@ -35,6 +41,7 @@ PI_ATTN_F32, PI_ATTN_BF16 = 0, 1
 
 _lock = threading.Lock()
 _lib = None
+_native = None   # the _binding module, once loaded
 
 
 class PiAttnError(RuntimeError):
@@ -92,6 +99,18 @@ def library() -> ctypes.CDLL:
             lib.pi_attn_backward_shard_kv.restype = ctypes.c_int
             _lib = lib
     return _lib
+
+
+def _load_native():
+    """Load _binding.so (and with it torch), built beside the library."""
+    global _native
+    library()
+    if not os.path.exists(BINDING_PATH):
+        raise RuntimeError(f"{BINDING_PATH} is not built; run `python -m paper_2511_10696_amd.build`")
+    import torch  # noqa: F401  (its libraries resolve the module's symbols)
+    from . import _binding
+    _native = _binding
+    return _binding
 
 
 def pi_attn_strerror(status: int) -> str:
@@ -181,6 +200,10 @@ def pi_attn_forward(q, k, v, gate, k_window: int, pi: int, scale: float | None =
     (per head) or [B, H, N] (per query), any strides.  Returns out
     [B, H, N, D] in the input dtype (and lse [B, H, N] float32 on request).
     """
+    r = (_native or _load_native()).forward(q, k, v, gate, k_window, pi, scale, logit_clamp, out, return_lse, lse,
+                                            stream, causal)
+    if r is not None:
+        return r
     torch = _torch()
     _require_cuda(q, k, v, gate, out, lse)
     if q.dim() != 4 or k.shape != q.shape or v.shape != q.shape:
@@ -354,6 +377,10 @@ def pi_attn_forward_gated(q, k, v, u, w2, b2, k_window: int, pi: int, scale: flo
     [B, H, N] float32) and lse on request; gate_logits is the ``gate`` that
     pi_attn_backward takes.
     """
+    r = (_native or _load_native()).forward_gated(q, k, v, u, w2, b2, k_window, pi, scale, logit_clamp, out,
+                                                  return_lse, lse, gate_out, stream, causal)
+    if r is not None:
+        return r
     torch = _torch()
     _require_cuda(q, k, v, u, w2, b2, out, lse, gate_out)
     if q.dim() != 4 or k.shape != q.shape or v.shape != q.shape:
@@ -410,6 +437,10 @@ def pi_attn_backward(q, k, v, gate, k_window: int, pi: int, out, lse, dout, scal
     ``gate_grad_per_query``.  dq, dk, dv, dgate (per query) and the row-term
     workspace rowterm may be passed as contiguous float32 buffers to fill.
     """
+    r = (_native or _load_native()).backward(q, k, v, gate, k_window, pi, out, lse, dout, scale, logit_clamp,
+                                             gate_grad_per_query, stream, causal, dq, dk, dv, dgate, rowterm)
+    if r is not None:
+        return r
     torch = _torch()
     _require_cuda(q, k, v, gate, out, dout, lse)
     if (q.dim() != 4 or k.shape != q.shape or v.shape != q.shape or dout.shape != q.shape
@@ -506,6 +537,10 @@ def pi_attn_decode_step(len_in, q_new, k_new, v_new, k_cache, v_cache, gate, k: 
                         out=None, lse=None, stream=None):
     """One decode step: appends k_new/v_new [S, H, D] as row len_in[s] of the
     caches [S, H, cap, D] and attends q_new over W_t.  Returns out [S, H, D]."""
+    r = (_native or _load_native()).decode_step(len_in, q_new, k_new, v_new, k_cache, v_cache, gate, k, pi, scale,
+                                                logit_clamp, len_out, out, lse, stream)
+    if r is not None:
+        return r
     torch = _torch()
     _require_cuda(len_in, q_new, k_new, v_new, k_cache, v_cache, gate, len_out, out, lse)
     S, H, cap, D = k_cache.shape

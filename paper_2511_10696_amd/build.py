@@ -3,7 +3,9 @@
     python -m paper_2511_10696_amd.build          # or build() from Python
 
 Each ``csrc/*.hip`` is compiled to an object under ``_build/`` (in parallel)
-and linked into ``paper_2511_10696_amd/libpi_attn.so``.
+and linked into ``paper_2511_10696_amd/libpi_attn.so``; ``csrc/binding.cpp``,
+the native marshalling of torch tensors, becomes
+``paper_2511_10696_amd/_binding.so`` beside it.
 """
 from __future__ import annotations
 
@@ -12,6 +14,7 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -19,6 +22,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD_DIR = os.path.join(ROOT, "_build")
 LIB_PATH = os.path.join(PKG, "libpi_attn.so")
+BINDING_PATH = os.path.join(PKG, "_binding.so")
 ARCH = "gfx950"
 
 # Packed-FP32 VALU instructions are disabled for every kernel (hipcc would
@@ -72,6 +76,26 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_binding() -> None:
+    """_binding.so: host code against torch's C++ API and libpi_attn.so."""
+    import torch
+    tdir = os.path.dirname(torch.__file__)
+    includes = [os.path.join(tdir, "include"), os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
+                sysconfig.get_paths()["include"], os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include")]
+    tmp = BINDING_PATH + ".tmp"
+    cmd = [hipcc(), "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-I", os.path.join(ROOT, "include")]
+    for d in includes:
+        cmd += ["-isystem", d]
+    cmd += ["-shared", os.path.join(CSRC, "binding.cpp"), "-o", tmp, f"-L{PKG}", "-l:libpi_attn.so",
+            "-Wl,-rpath,$ORIGIN", f"-L{os.path.join(tdir, 'lib')}"]
+    cmd += [f"-l{x}" for x in ("c10", "c10_hip", "torch", "torch_cpu", "torch_python")]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"hipcc failed for binding.cpp:\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, BINDING_PATH)
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
     srcs = sources()
@@ -83,8 +107,9 @@ def build(verbose: bool = False) -> str:
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
     os.replace(tmp, LIB_PATH)
+    _build_binding()
     if verbose:
-        print(f"built {LIB_PATH}")
+        print(f"built {LIB_PATH} and {BINDING_PATH}")
     return LIB_PATH
 
 

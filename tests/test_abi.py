@@ -378,3 +378,13 @@ def test_default_scale(lib, D):
     import numpy as np
     got = pa.library().pi_attn_default_scale(D)
     assert got == (float(np.float32(1.0 / math.sqrt(D))) if D >= 1 else 0.0)
+
+
+def test_native_marshalling_declines_what_is_not_plain(lib):
+    """The native module returns None (the Python code then serves or words
+    the call) for CPU tensors, other argument types and wrong counts."""
+    native = pa._load_native()
+    x, g = torch.zeros(1, 1, 8, 64), torch.zeros(1)
+    assert native.forward(x, x, x, g, 2, 4, None, 0.0, None, False, None, None, True) is None
+    assert native.forward() is None and native.decode_step(1, 2, 3) is None
+    assert native.backward(*[None] * 19) is None and native.forward_gated(*[3.0] * 16) is None
