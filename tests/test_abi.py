@@ -383,6 +383,7 @@ def test_default_scale(lib, D):
 def test_native_marshalling_declines_what_is_not_plain(lib):
     """The native module returns None (the Python code then serves or words
     the call) for CPU tensors, other argument types and wrong counts."""
+    import torch
     native = pa._load_native()
     x, g = torch.zeros(1, 1, 8, 64), torch.zeros(1)
     assert native.forward(x, x, x, g, 2, 4, None, 0.0, None, False, None, None, True) is None
