@@ -38,6 +38,7 @@
 // chunk index are XORed with bits 2-3 of the row, which keeps both patterns
 // free of bank conflicts; the value tile, read as rows only, has rows padded
 // by 16 bytes.
+#include "bwd_tile.h"
 #include "kernels.h"
 #include "pi_common.h"
 
@@ -45,56 +46,31 @@ namespace pi_attn {
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+using namespace bwd;
 
-constexpr int WAVES = 4;
 constexpr int NT = 64 * WAVES;
 constexpr int BM = 32 * WAVES;
-constexpr int TK = 64;
 
 template <int D>
-struct Tile {
-    static constexpr int CPR = D / 8;         // 16-byte chunks per row
-    static constexpr int KROW = 2 * D + 64;   // key-tile LDS row stride (bytes)
-    static constexpr int VROW = 2 * D + 16;   // value-tile LDS row stride (bytes)
-    static constexpr int KS = D / 16;         // k-steps of the score products
-    static constexpr int DB = D / 32;         // 32-dim output blocks
+struct VTile {
+    static constexpr int ROW = 2 * D + 16;   // value-tile LDS row stride (bytes)
 };
 
 template <int D>
 struct TileBuf {
-    alignas(16) unsigned char k[TK * Tile<D>::KROW];
-    alignas(16) unsigned char v[TK * Tile<D>::VROW];
+    alignas(16) unsigned char k[Tile<D>::BYTES];
+    alignas(16) unsigned char v[TK * VTile<D>::ROW];
 };
 
-// Key-tile chunk swizzle: chunk pc of row r sits at chunk pc ^ chunk_x(r).
-__device__ inline int chunk_x(int row) { return (row >> 2) & 3; }
-
-// Fetch tile rows [row0, row0 + TK) (counted from the window start) into
-// LDS buffer tb: instruction u of a tensor fills bytes [1024u, 1024u + 1024)
-// of its buffer, 16 bytes per lane, each lane's source chosen so that the
-// bytes land in the tile's layout (pad chunks take an out-of-range offset
-// and are written as zeros); wavefront w issues u = w, w + WAVES, ...
+// Fetch tile rows [row0, row0 + TK) (counted from the window start) into LDS
+// buffer tb, the value tile's rows padded by 16 bytes and not swizzled.
 template <int D>
 __device__ inline void tile_fetch(TileBuf<D> &tb, u32x4 rk, u32x4 rv, int rowb, int row0, int w, int lane) {
     using T = Tile<D>;
-    constexpr int KU = T::KROW / 16, VU = T::VROW / 16;   // LDS chunks per row
-    constexpr int KI = TK * KU / 64, VI = TK * VU / 64;   // instructions per tile
-    static_assert(TK * KU % 64 == 0 && TK * VU % 64 == 0, "tile fetch shape");
-#pragma unroll
-    for (int u0 = 0; u0 < KI; u0 += WAVES) {
-        const int u = u0 + w;
-        if (u < KI) {   // wave-uniform
-            const int pidx = 64 * u + lane, row = pidx / KU, pc = pidx % KU;
-            const int off = pc < T::CPR ? (row0 + row) * rowb + (pc ^ chunk_x(row)) * 16 : kOutOfRange;
-            lds_fetch16(rk, off, tb.k + 1024 * u);
-        }
-    }
+    constexpr int VU = VTile<D>::ROW / 16;   // LDS chunks per row
+    constexpr int VI = TK * VU / 64;         // instructions per tile
+    static_assert(TK * VU % 64 == 0, "tile fetch shape");
+    fetch_tile<D, false>(tb.k, rk, rowb, row0, w, lane);
 #pragma unroll
     for (int u0 = 0; u0 < VI; u0 += WAVES) {
         const int u = u0 + w;
@@ -106,67 +82,13 @@ __device__ inline void tile_fetch(TileBuf<D> &tb, u32x4 rk, u32x4 rv, int rowb, 
     }
 }
 
-__device__ inline float other_half(float x) {
-    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(__lane_id() < 32 ? p[1] : p[0]);
-}
-
-// acc + <a, b> over eight bf16 pairs (packed products, fp32 sums).
-__device__ inline float dot_bf16x8(const bf16x8 &a, const bf16x8 &b, float acc) {
-    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 0, 1), __builtin_shufflevector(b, b, 0, 1),
-                                          acc, false);
-    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 2, 3), __builtin_shufflevector(b, b, 2, 3),
-                                          acc, false);
-    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 4, 5), __builtin_shufflevector(b, b, 4, 5),
-                                          acc, false);
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 6, 7), __builtin_shufflevector(b, b, 6, 7),
-                                           acc, false);
-}
-
 // Row fragments (A operand, row l%32, dims 16s + 8(l/32)) of 32-row block
-// `blk` of the value tile ...
+// `blk` of the value tile.
 template <int D>
 __device__ inline void read_vrows(bf16x8 f[Tile<D>::KS], const unsigned char *tile, int blk, int c, int g) {
-    const unsigned char *base = tile + (32 * blk + c) * Tile<D>::VROW + 16 * g;
+    const unsigned char *base = tile + (32 * blk + c) * VTile<D>::ROW + 16 * g;
 #pragma unroll
     for (int s = 0; s < Tile<D>::KS; ++s) f[s] = *reinterpret_cast<const bf16x8 *>(base + 32 * s);
-}
-
-// ... and of the key tile: chunk (2s + g) ^ x = 2(s ^ (x >> 1)) + (g ^ (x & 1)),
-// x = chunk_x(row), so even and odd k-steps have one base each.
-template <int D>
-__device__ inline void read_krows(bf16x8 f[Tile<D>::KS], const unsigned char *tile, int blk, int c, int g) {
-    const int row = 32 * blk + c, x = chunk_x(row);
-    const int rb = row * Tile<D>::KROW + 16 * (g ^ (x & 1));
-    const int rbo[2] = {rb + 32 * (x >> 1), rb - 32 * (x >> 1)};
-#pragma unroll
-    for (int s = 0; s < Tile<D>::KS; ++s) f[s] = *reinterpret_cast<const bf16x8 *>(tile + rbo[s & 1] + 32 * s);
-}
-
-// Transposed fragments (A operand: dim 32db + l%32, keys 16cc + {4g..4g+3,
-// 8+4g..8+4g+3}) of 32-row block `blk` of the key tile by LDS transpose
-// reads: rows 32 blk + 4g + r + 8hh + 16cc, whose chunk_x is g + 2hh.
-template <int D>
-__device__ inline void read_cols(bf16x8 f[2][Tile<D>::DB], const unsigned char *tile, int blk, int lane) {
-    const int g = lane >> 5, G = lane >> 4, r = (lane >> 2) & 3, qd = lane & 3;
-    const int jq = 2 * (G & 1) + (qd >> 1);
-    const int toff[2] = {(32 * blk + 4 * g + r) * Tile<D>::KROW + 16 * (jq ^ g) + (qd & 1) * 8,
-                         (32 * blk + 4 * g + r + 8) * Tile<D>::KROW + 16 * (jq ^ (g + 2)) + (qd & 1) * 8};
-#pragma unroll
-    for (int cc = 0; cc < 2; ++cc) {
-#pragma unroll
-        for (int db = 0; db < Tile<D>::DB; ++db) {
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-                const unsigned char *src = tile + toff[hh] + 16 * cc * Tile<D>::KROW + 64 * db;
-                const bf16x4 y = __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)src));
-                f[cc][db][4 * hh + 0] = y[0];
-                f[cc][db][4 * hh + 1] = y[1];
-                f[cc][db][4 * hh + 2] = y[2];
-                f[cc][db][4 * hh + 3] = y[3];
-            }
-        }
-    }
 }
 
 template <int D, bool CLAMP, bool BIDIR>
@@ -283,33 +205,10 @@ __global__ __launch_bounds__(NT, 2) void backward_q_bf16_kernel(BwdParams bp, in
             a_par += cut ? 0.0f : wgt * dpd;
             b_par += cut ? 0.0f : wgt;
         }
-        // dq += dd * k_p over this lane's dims 32db + 8i + 4g + [0, 4): the
-        // 8-dim group m = 4db + i, whose half 4g..4g+3 this lane needs, is
-        // held whole by lane (c, m & 1) in kpf[m >> 1]; each lane keeps its
-        // own half of its groups and takes the other half from the other
-        // half of the wavefront
-        const auto kh = [&](int s2) { return __builtin_bit_cast(uint4, has_p ? kpf[s2] : bf16x8{}); };
+        // dq += dd * k_p (no key where there is no partner: zeros)
 #pragma unroll
-        for (int s2 = 0; s2 < KS; ++s2) {
-            const uint4 own = kh(s2);
-            // lane g = 0 sends dims 4..7 of its group, lane g = 1 dims 0..3
-            const uint2 send = g == 0 ? make_uint2(own.z, own.w) : make_uint2(own.x, own.y);
-            const uint2 recv = make_uint2(__float_as_uint(other_half(__uint_as_float(send.x))),
-                                          __float_as_uint(other_half(__uint_as_float(send.y))));
-            // groups 2 s2 (held by g = 0) and 2 s2 + 1 (held by g = 1)
-            const uint2 lo = g == 0 ? make_uint2(own.x, own.y) : recv;   // group 2 s2, dims 4g..4g+3
-            const uint2 hi = g == 0 ? recv : make_uint2(own.z, own.w);   // group 2 s2 + 1
-#pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                const int m = 2 * s2 + half;
-                const uint2 raw = half ? hi : lo;
-                const int db = m >> 2, i = m & 3;
-                dq[db][4 * i + 0] += dd * __uint_as_float(raw.x << 16);
-                dq[db][4 * i + 1] += dd * __uint_as_float(raw.x & 0xffff0000u);
-                dq[db][4 * i + 2] += dd * __uint_as_float(raw.y << 16);
-                dq[db][4 * i + 3] += dd * __uint_as_float(raw.y & 0xffff0000u);
-            }
-        }
+        for (int s = 0; s < KS; ++s) kpf[s] = has_p ? kpf[s] : bf16x8{};
+        add_row<D>(dq, kpf, dd, g);
     };
     partner(t - pi, partner_enabled(kw, pi) && t - pi >= 0 && t_ok);
     if constexpr (BIDIR) partner(t + pi, t_ok && partner_fwd_of(t, kw, pi, NS) >= 0);
@@ -322,7 +221,7 @@ __global__ __launch_bounds__(NT, 2) void backward_q_bf16_kernel(BwdParams bp, in
         const bool edge = BIDIR ? !(j0 + 31 - q0 <= kw && q0 + 31 - j0 <= kw) || q0 + 31 >= NQ || j0 + 31 >= NS
                                 : !(j0 + 31 <= q0 && j0 >= q0 + 31 - kw) || q0 + 31 >= NQ;
         bf16x8 f[KS];
-        read_krows<D>(f, tb.k, blk, c, g);
+        read_rows<D>(f, tb.k, blk, c, g);
         f32x16 sc = {};
 #pragma unroll
         for (int s = 0; s < KS; ++s) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[s], qf[s], sc, 0, 0, 0);

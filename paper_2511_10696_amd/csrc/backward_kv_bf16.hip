@@ -33,6 +33,8 @@
 // wavefronts fit each SIMD and one's exponentials and conversions run while
 // the other's MFMAs do.  Every block is two phases split by a work-group
 // barrier: S and dP, then dV and dK; alpha^ is double-buffered by block.
+#include <algorithm>
+
 #include "kernels.h"
 #include "pi_common.h"
 
@@ -225,7 +227,7 @@ __global__ __launch_bounds__(NT) void backward_kv_bf16_kernel(BwdParams bp, int 
             tb.r[tid] = st.r;
             const float bias_local = fb.local, bias_partner = fb.partner;
             const float bias = st.band ? bias_local : bias_partner;
-            tb.bias[tid] = CLAMP ? bias : bias * kLog2e - l2;
+            tb.bias[tid] = CLAMP ? bias : __builtin_fmaf(bias, kLog2e, -l2);
         }
     };
 
@@ -525,6 +527,16 @@ hipError_t launch_kvc(const BwdParams &p, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_backward_kv_bf16(const BwdParams &p, hipStream_t stream) {
+    // D = 64: one wavefront per 32 keys once every CU has a work-group.  Below
+    // that a launch takes as long as one work-group's chain of tiles, which
+    // the pairs split (10.6 against 11.8 us at B1 H4 N500 k64, 12.5 against
+    // 14.0 us at B1 H8 N2048; above, 24.4 against 18.4 us at 384 work-groups).
+    // Its tiles of dL/dy lie within 32-bit byte offsets (the callers have
+    // checked q's stride for that).
+    const int64_t groups = (int64_t)p.f.B * p.f.H * ((p.f.N + BK - 1) / BK);
+    const int64_t rows = (p.f.causal ? 1 : 2) * (int64_t)std::min(p.f.k, p.f.nseq) + 256;
+    if (p.f.D == 64 && groups > 256 && rows * p.osn * 2 < ((int64_t)1 << 31))
+        return launch_backward_kv64_bf16(p, stream);
     if (p.f.D == 64) return p.f.causal ? launch_kvc<64, false>(p, stream) : launch_kvc<64, true>(p, stream);
     return p.f.causal ? launch_kvc<128, false>(p, stream) : launch_kvc<128, true>(p, stream);
 }

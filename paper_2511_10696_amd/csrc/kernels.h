@@ -88,4 +88,8 @@ hipError_t launch_backward_q_bf16(const BwdParams &p, hipStream_t stream);
 // MFMA key pass (dk, dv) for bf16 inputs; needs the row terms.
 hipError_t launch_backward_kv_bf16(const BwdParams &p, hipStream_t stream);
 
+// The same at D = 64, one wavefront per 32 keys; rows of dL/dy within 32-bit
+// byte offsets of a band's first row.
+hipError_t launch_backward_kv64_bf16(const BwdParams &p, hipStream_t stream);
+
 }  // namespace pi_attn
