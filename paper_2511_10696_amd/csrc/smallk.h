@@ -35,4 +35,8 @@ hipError_t launch_gate_logits(const FwdParams &p, const GateMlp &mlp, int dtype,
 // forward's work decomposition.  Needs the forward's lse.
 hipError_t launch_backward_smallk(const BwdParams &p, hipStream_t stream);
 
+// The same in one pass over the sequence, and whether it takes the call.
+bool smallk_fused_takes(const BwdParams &p);
+hipError_t launch_backward_smallk_fused(const BwdParams &p, hipStream_t stream);
+
 }  // namespace pi_attn

@@ -34,18 +34,6 @@ namespace {
 
 using namespace sk;
 
-// Prior derivatives of one gate logit: d log alpha~/dg and d log(1 - alpha~)/dg.
-struct GateDeriv {
-    float local, partner;
-};
-
-__device__ inline GateDeriv gate_deriv(float g) {
-    const float a = 1.0f / (1.0f + __expf(-g));
-    const float at = kGateEps + (1.0f - 2.0f * kGateEps) * a;
-    const float c = (1.0f - 2.0f * kGateEps) * a * (1.0f - a);
-    return GateDeriv{c / at, -c / (1.0f - at)};
-}
-
 // Work-group -> (b, tile, head group) with at least ceil(H / 32) groups and
 // more while the grid is small (as in the forward).
 struct Grid {
@@ -60,18 +48,6 @@ inline Grid make_grid(const FwdParams &f) {
     while (g.n_hg < f.H && (int64_t)f.B * g.n_tt * g.n_hg < 2048) ++g.n_hg;
     g.n_logical = (int64_t)f.B * g.n_tt * g.n_hg;
     return g;
-}
-
-// Fused logit in log2 units of one entry from its dot product: clamped with
-// the exact prior, or shifted (see fusion_bias); `cut` when it saturates.
-__device__ inline float logit2(float dot, float bias, const FwdParams &f, bool clamp_on, bool &cut) {
-    if (clamp_on) {
-        const float dl = fminf(fmaxf(dot * f.scale + bias, -f.clamp), f.clamp);
-        cut = fabsf(dl) >= f.clamp;
-        return dl * kLog2e;
-    }
-    cut = false;
-    return __builtin_fmaf(dot, f.scale * kLog2e, bias * kLog2e);
 }
 
 // ---------------------------------------------------------------------------
@@ -458,6 +434,7 @@ hipError_t launch_mode(const BwdParams &p, hipStream_t stream) {
 
 hipError_t launch_backward_smallk(const BwdParams &p, hipStream_t stream) {
     if ((int64_t)p.f.B * p.f.H * p.f.N == 0) return hipSuccess;
+    if (smallk_fused_takes(p)) return launch_backward_smallk_fused(p, stream);
     if (p.f.D == 64) return p.f.causal ? launch_mode<64, false>(p, stream) : launch_mode<64, true>(p, stream);
     return p.f.causal ? launch_mode<128, false>(p, stream) : launch_mode<128, true>(p, stream);
 }
