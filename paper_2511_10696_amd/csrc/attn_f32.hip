@@ -42,16 +42,16 @@ struct KeyBlock {
 };
 
 template <int D, bool SPLIT>
-__global__ __launch_bounds__(NT, D == 64 && !SPLIT ? 4 : 2) void forward_f32_kernel(FwdParams p, int n_qt, int64_t n_tiles, int64_t n_logical) {
-    const int64_t logical = xcd_remap(blockIdx.x, n_logical);
-    if (logical < 0) return;
+__global__ __launch_bounds__(NT, D == 64 && !SPLIT ? 4 : 2) void forward_f32_kernel(FwdParams p, int n_qt, uint32_t n_tiles, uint32_t n_logical) {
+    const uint32_t logical = xcd_remap(blockIdx.x, n_logical);
+    if (logical >= n_logical) return;
     const int lane = __lane_id(), c = lane & 15, g = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t tile = SPLIT ? logical : logical * WAVES + w;
+    const uint32_t tile = SPLIT ? logical : logical * WAVES + w;
     if (tile >= n_tiles) return;   // never with SPLIT: the whole work-group stays for the merge
-    const int q0 = (int)(tile % n_qt) * TILE;
-    const int64_t bh = tile / n_qt;
-    const int h = (int)(bh % p.H), b = (int)(bh / p.H);
+    const DivMod tile_of = divmod(tile, n_qt), head_of = divmod(tile_of.quot, p.H);
+    const int q0 = (int)tile_of.rem * TILE, h = (int)head_of.rem, b = (int)head_of.quot;
+    const int64_t bh = tile_of.quot;
     const int t = q0 + c, N = p.N;
     const bool t_ok = t < N;
     const int tq = t_ok ? t : N - 1;
@@ -177,7 +177,7 @@ hipError_t launch_fwd(const FwdParams &p, hipStream_t stream) {
     const bool split = n_tiles <= kSplitTiles;
     const int64_t n_logical = split ? n_tiles : (n_tiles + WAVES - 1) / WAVES;
     return launch_kernel(split ? forward_f32_kernel<D, true> : forward_f32_kernel<D, false>,
-                         dim3((unsigned)xcd_grid(n_logical)), dim3(NT), stream, p, n_qt, n_tiles, n_logical);
+                         dim3((unsigned)xcd_grid(n_logical)), dim3(NT), stream, p, n_qt, (uint32_t)n_tiles, (uint32_t)n_logical);
 }
 
 }  // namespace

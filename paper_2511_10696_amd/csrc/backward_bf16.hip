@@ -92,16 +92,16 @@ __device__ inline void read_vrows(bf16x8 f[Tile<D>::KS], const unsigned char *ti
 }
 
 template <int D, bool CLAMP, bool BIDIR>
-__global__ __launch_bounds__(NT, 2) void backward_q_bf16_kernel(BwdParams bp, int n_qt, int64_t n_logical) {
+__global__ __launch_bounds__(NT, 2) void backward_q_bf16_kernel(BwdParams bp, int n_qt, uint32_t n_logical) {
     using T = Tile<D>;
     constexpr int KS = T::KS, DB = T::DB;
     const FwdParams &p = bp.f;
     __shared__ TileBuf<D> tA, tB;
-    const int64_t logical = xcd_remap(blockIdx.x, n_logical);
-    if (logical < 0) return;
-    const int qt = (int)(logical % n_qt);
-    const int64_t bh = logical / n_qt;
-    const int h = (int)(bh % p.H), b = (int)(bh / p.H);
+    const uint32_t logical = xcd_remap(blockIdx.x, n_logical);
+    if (logical >= n_logical) return;
+    const DivMod tile_of = divmod(logical, n_qt), head_of = divmod(tile_of.quot, p.H);
+    const int qt = (int)tile_of.rem, h = (int)head_of.rem, b = (int)head_of.quot;
+    const int64_t bh = tile_of.quot;
 
     const int tid = threadIdx.x;
     const int lane = __lane_id();
@@ -319,7 +319,7 @@ hipError_t launch_q(const BwdParams &p, hipStream_t stream) {
     const int64_t n_logical = (int64_t)p.f.B * p.f.H * n_qt;
     const int64_t grid = xcd_grid(n_logical);
     return launch_kernel(backward_q_bf16_kernel<D, CLAMP, BIDIR>, dim3((unsigned)grid), dim3(NT), stream, p, n_qt,
-                         n_logical);
+                         (uint32_t)n_logical);
 }
 
 template <int D, bool BIDIR>

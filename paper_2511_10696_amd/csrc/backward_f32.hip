@@ -65,18 +65,18 @@ __device__ inline float weight(float dot, float bias, float shift, const FwdPara
 
 // ---- query pass -----------------------------------------------------------------
 template <int D, bool SPLIT>
-__global__ __launch_bounds__(NT, D == 64 && !SPLIT ? 4 : 2) void backward_q_f32_kernel(BwdParams bp, int n_qt, int64_t n_tiles,
-                                                            int64_t n_logical) {
+__global__ __launch_bounds__(NT, D == 64 && !SPLIT ? 4 : 2) void backward_q_f32_kernel(BwdParams bp, int n_qt, uint32_t n_tiles,
+                                                            uint32_t n_logical) {
     const FwdParams &p = bp.f;
-    const int64_t logical = xcd_remap(blockIdx.x, n_logical);
-    if (logical < 0) return;
+    const uint32_t logical = xcd_remap(blockIdx.x, n_logical);
+    if (logical >= n_logical) return;
     const int lane = __lane_id(), c = lane & 15, g = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t tile = SPLIT ? logical : logical * WAVES + w;
+    const uint32_t tile = SPLIT ? logical : logical * WAVES + w;
     if (tile >= n_tiles) return;   // never with SPLIT
-    const int q0 = (int)(tile % n_qt) * TILE;
-    const int64_t bh = tile / n_qt;
-    const int h = (int)(bh % p.H), b = (int)(bh / p.H);
+    const DivMod tile_of = divmod(tile, n_qt), head_of = divmod(tile_of.quot, p.H);
+    const int q0 = (int)tile_of.rem * TILE, h = (int)head_of.rem, b = (int)head_of.quot;
+    const int64_t bh = tile_of.quot;
     const int t = q0 + c, N = p.N;
     const bool t_ok = t < N;
     const int tq = t_ok ? t : N - 1;
@@ -184,18 +184,18 @@ __global__ __launch_bounds__(NT, D == 64 && !SPLIT ? 4 : 2) void backward_q_f32_
 
 // ---- key pass -------------------------------------------------------------------
 template <int D, bool SPLIT>
-__global__ __launch_bounds__(NT) void backward_kv_f32_kernel(BwdParams bp, int n_kt, int64_t n_tiles,
-                                                             int64_t n_logical) {
+__global__ __launch_bounds__(NT) void backward_kv_f32_kernel(BwdParams bp, int n_kt, uint32_t n_tiles,
+                                                             uint32_t n_logical) {
     const FwdParams &p = bp.f;
-    const int64_t logical = xcd_remap(blockIdx.x, n_logical);
-    if (logical < 0) return;
+    const uint32_t logical = xcd_remap(blockIdx.x, n_logical);
+    if (logical >= n_logical) return;
     const int lane = __lane_id(), c = lane & 15, g = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t tile = SPLIT ? logical : logical * WAVES + w;
+    const uint32_t tile = SPLIT ? logical : logical * WAVES + w;
     if (tile >= n_tiles) return;   // never with SPLIT
-    const int j0 = (int)(tile % n_kt) * TILE;
-    const int64_t bh = tile / n_kt;
-    const int h = (int)(bh % p.H), b = (int)(bh / p.H);
+    const DivMod tile_of = divmod(tile, n_kt), head_of = divmod(tile_of.quot, p.H);
+    const int j0 = (int)tile_of.rem * TILE, h = (int)head_of.rem, b = (int)head_of.quot;
+    const int64_t bh = tile_of.quot;
     const int j = j0 + c, N = p.N;
     const bool j_ok = j < N;
     const int jq = j_ok ? j : N - 1;
@@ -319,9 +319,9 @@ hipError_t launch(const BwdParams &p, hipStream_t stream) {
     const int64_t n_logical = SPLIT ? n_tiles : (n_tiles + WAVES - 1) / WAVES;
     const dim3 grid((unsigned)xcd_grid(n_logical)), block(NT);
     const hipError_t e =
-        launch_kernel(backward_q_f32_kernel<D, SPLIT>, grid, block, stream, p, n_t, n_tiles, n_logical);
+        launch_kernel(backward_q_f32_kernel<D, SPLIT>, grid, block, stream, p, n_t, (uint32_t)n_tiles, (uint32_t)n_logical);
     if (e != hipSuccess) return e;
-    return launch_kernel(backward_kv_f32_kernel<D, SPLIT>, grid, block, stream, p, n_t, n_tiles, n_logical);
+    return launch_kernel(backward_kv_f32_kernel<D, SPLIT>, grid, block, stream, p, n_t, (uint32_t)n_tiles, (uint32_t)n_logical);
 }
 
 template <int D>

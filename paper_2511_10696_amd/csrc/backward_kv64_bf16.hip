@@ -56,14 +56,14 @@ struct TileBuf {
 };
 
 template <bool CLAMP, bool BIDIR>
-__global__ __launch_bounds__(NT, 2) void backward_kv64_bf16_kernel(BwdParams bp, int n_kt, int64_t n_logical) {
+__global__ __launch_bounds__(NT, 2) void backward_kv64_bf16_kernel(BwdParams bp, int n_kt, uint32_t n_logical) {
     const FwdParams &p = bp.f;
     __shared__ TileBuf tA, tB;
-    const int64_t logical = xcd_remap(blockIdx.x, n_logical);
-    if (logical < 0) return;
-    const int kt = (int)(logical % n_kt);
-    const int64_t bh = logical / n_kt;
-    const int h = (int)(bh % p.H), b = (int)(bh / p.H);
+    const uint32_t logical = xcd_remap(blockIdx.x, n_logical);
+    if (logical >= n_logical) return;
+    const DivMod tile_of = divmod(logical, n_kt), head_of = divmod(tile_of.quot, p.H);
+    const int kt = (int)tile_of.rem, h = (int)head_of.rem, b = (int)head_of.quot;
+    const int64_t bh = tile_of.quot;
 
     const int tid = threadIdx.x;
     const int lane = __lane_id();
@@ -331,7 +331,8 @@ hipError_t launch(const BwdParams &p, hipStream_t stream) {
     const int n_kt = (p.f.N + BK - 1) / BK;
     const int64_t n_logical = (int64_t)p.f.B * p.f.H * n_kt;
     return launch_kernel(p.f.causal ? backward_kv64_bf16_kernel<CLAMP, false> : backward_kv64_bf16_kernel<CLAMP, true>,
-                         dim3((unsigned)xcd_grid(n_logical)), dim3(NT), stream, p, n_kt, n_logical);
+                         dim3((unsigned)xcd_grid(n_logical)), dim3(NT), stream, p, n_kt,
+                         (uint32_t)n_logical);
 }
 
 }  // namespace

@@ -116,17 +116,17 @@ __device__ inline float dot_bf16x8(const bf16x8 &a, const bf16x8 &b, float acc) 
 }
 
 template <int D, bool CLAMP, bool BIDIR>
-__global__ __launch_bounds__(NT) void backward_kv_bf16_kernel(BwdParams bp, int n_kt, int64_t n_logical) {
+__global__ __launch_bounds__(NT) void backward_kv_bf16_kernel(BwdParams bp, int n_kt, uint32_t n_logical) {
     using T = Tile<D>;
     constexpr int KS = T::KS, DB = T::DB;
     const FwdParams &p = bp.f;
     __shared__ QTile<D> tA, tB;
     __shared__ PBuf pbuf;
-    const int64_t logical = xcd_remap(blockIdx.x, n_logical);
-    if (logical < 0) return;
-    const int kt = (int)(logical % n_kt);
-    const int64_t bh = logical / n_kt;
-    const int h = (int)(bh % p.H), b = (int)(bh / p.H);
+    const uint32_t logical = xcd_remap(blockIdx.x, n_logical);
+    if (logical >= n_logical) return;
+    const DivMod tile_of = divmod(logical, n_kt), head_of = divmod(tile_of.quot, p.H);
+    const int kt = (int)tile_of.rem, h = (int)head_of.rem, b = (int)head_of.quot;
+    const int64_t bh = tile_of.quot;
 
     const int tid = threadIdx.x;
     const int lane = __lane_id();
@@ -517,7 +517,7 @@ hipError_t launch_kv(const BwdParams &p, hipStream_t stream) {
     const int64_t n_logical = (int64_t)p.f.B * p.f.H * n_kt;
     const int64_t grid = xcd_grid(n_logical);
     return launch_kernel(backward_kv_bf16_kernel<D, CLAMP, BIDIR>, dim3((unsigned)grid), dim3(NT), stream, p, n_kt,
-                         n_logical);
+                         (uint32_t)n_logical);
 }
 
 template <int D, bool BIDIR>

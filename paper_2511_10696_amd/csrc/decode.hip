@@ -91,7 +91,8 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kernel(DecodeParams p) {
     __shared__ float s_acc[WAVES][D];
 
     const int64_t sh = blockIdx.x;
-    const int s = (int)(sh / p.H), h = (int)(sh % p.H);
+    const DivMod head_of = divmod(blockIdx.x, p.H);
+    const int s = (int)head_of.quot, h = (int)head_of.rem;
     const int tid = threadIdx.x, lane = __lane_id();
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int sub = lane % LPR, rg = lane / LPR;

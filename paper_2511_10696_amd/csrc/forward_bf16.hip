@@ -251,15 +251,15 @@ __device__ inline void softmax_block(Wave<D> &ws, f32x16 &s, bool edge, int j0, 
 }
 
 template <int D, bool CLAMP, bool BIDIR, bool LSE>
-__global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void forward_bf16_kernel(FwdParams p, int n_qt, int64_t n_logical) {
+__global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void forward_bf16_kernel(FwdParams p, int n_qt, uint32_t n_logical) {
     using T = Tile<D>;
     using W = Wave<D>;
     __shared__ TileBuf<D> tA, tB;
-    const int64_t logical = xcd_remap(blockIdx.x, n_logical);
-    if (logical < 0) return;
-    const int qt = (int)(logical % n_qt);
-    const int64_t bh = logical / n_qt;
-    const int h = (int)(bh % p.H), b = (int)(bh / p.H);
+    const uint32_t logical = xcd_remap(blockIdx.x, n_logical);
+    if (logical >= n_logical) return;
+    const DivMod tile_of = divmod(logical, n_qt), head_of = divmod(tile_of.quot, p.H);
+    const int qt = (int)tile_of.rem, h = (int)head_of.rem, b = (int)head_of.quot;
+    const int64_t bh = tile_of.quot;
 
     const int tid = threadIdx.x;
     const int lane = __lane_id();
@@ -530,7 +530,7 @@ hipError_t launch(const FwdParams &p, hipStream_t stream) {
     if (n_logical == 0) return hipSuccess;
     const int64_t grid = xcd_grid(n_logical);
     return launch_kernel(forward_bf16_kernel<D, CLAMP, BIDIR, LSE>, dim3((unsigned)grid), dim3(NT), stream, p, n_qt,
-                         n_logical);
+                         (uint32_t)n_logical);
 }
 
 template <int D, bool BIDIR, bool LSE>

@@ -92,18 +92,30 @@ __device__ inline FusionBias fusion_bias(float g, bool exact) {
 // round-robin over the 8 XCDs; this remaps them so that each XCD receives a
 // contiguous range of logical tiles (neighbouring query tiles share most of
 // their keys, which then stay in that XCD's L2).  The grid is padded to a
-// multiple of 8; ids mapping past n_logical return -1.
+// multiple of 8; ids mapping past n_logical return a value >= n_logical and
+// have no work.  Logical tiles and everything decoded from them are 32-bit (a
+// problem has fewer than 2^31 rows): 64-bit divisions by run-time counts were
+// a third of a short tile's scalar instructions.
 constexpr int kNumXcd = 8;
 
-__device__ inline int64_t xcd_remap(int64_t bid, int64_t n_logical) {
-    int64_t per = (n_logical + kNumXcd - 1) / kNumXcd;
-    int64_t logical = (bid % kNumXcd) * per + bid / kNumXcd;
-    return logical < n_logical ? logical : -1;
+__device__ inline uint32_t xcd_remap(uint32_t bid, uint32_t n_logical) {
+    const uint32_t per = (n_logical + kNumXcd - 1) / kNumXcd;
+    return (bid % kNumXcd) * per + bid / kNumXcd;
 }
 
 inline int64_t xcd_grid(int64_t n_logical) {
     int64_t per = (n_logical + kNumXcd - 1) / kNumXcd;
     return per * kNumXcd;
+}
+
+// Quotient and remainder of a wave-uniform index (kept in scalar registers).
+struct DivMod {
+    uint32_t quot, rem;
+};
+
+__device__ inline DivMod divmod(uint32_t x, uint32_t d) {
+    const uint32_t q = __builtin_amdgcn_readfirstlane(x / d);
+    return DivMod{q, x - q * d};
 }
 
 // ---- direct global-to-LDS tile fetch ---------------------------------------

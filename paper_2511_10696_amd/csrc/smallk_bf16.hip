@@ -78,17 +78,16 @@ __device__ void gate_tile(const FwdParams &p, const GateMlp &m, int b, int t0, i
 
 template <int D, bool BIDIR, bool GATED, int KMAX>
 __global__ __launch_bounds__(NT) void smallk_bf16_kernel(FwdParams p, GateMlp m, int n_tt, int n_hg,
-                                                         int64_t n_logical) {
+                                                         uint32_t n_logical) {
     using BD = Band<D, BIDIR, KMAX>;
     constexpr int E = BD::E, CPR = BD::CPR, ROWB = BD::ROWB;
     __shared__ alignas(16) unsigned char band[2][2][BD::ROWS * ROWB];   // [buffer][K, V]
     __shared__ float glds[HG * TT];
     static_assert(sizeof(band) >= kGateScratch * sizeof(float), "the gate prologue borrows the band buffers");
-    const int64_t logical = xcd_remap(blockIdx.x, n_logical);
-    if (logical < 0) return;
-    const int hg = (int)(logical % n_hg);
-    const int tt = (int)((logical / n_hg) % n_tt);
-    const int b = (int)(logical / ((int64_t)n_hg * n_tt));
+    const uint32_t logical = xcd_remap(blockIdx.x, n_logical);
+    if (logical >= n_logical) return;
+    const DivMod group_of = divmod(logical, n_hg), tile_of = divmod(group_of.quot, n_tt);
+    const int hg = (int)group_of.rem, tt = (int)tile_of.rem, b = (int)tile_of.quot;
     const int N = p.N, kw = p.k, pi = p.pi;
     const int hpg = (p.H + n_hg - 1) / n_hg;   // heads per group
     const int h0 = hg * hpg, h1 = min(p.H, h0 + hpg);
@@ -308,7 +307,7 @@ hipError_t launch_sk(const FwdParams &p, const GateMlp &m, hipStream_t stream) {
     const int64_t n_logical = (int64_t)p.B * n_tt * n_hg;
     const int64_t grid = xcd_grid(n_logical);
     return launch_kernel(smallk_bf16_kernel<D, BIDIR, GATED, KMAX>, dim3((unsigned)grid), dim3(NT), stream, p, m,
-                         n_tt, n_hg, n_logical);
+                         n_tt, n_hg, (uint32_t)n_logical);
 }
 
 template <int D, bool BIDIR, bool GATED>

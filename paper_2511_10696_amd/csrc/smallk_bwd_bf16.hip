@@ -38,7 +38,7 @@ using namespace sk;
 // more while the grid is small (as in the forward).
 struct Grid {
     int n_tt, n_hg;
-    int64_t n_logical;
+    uint32_t n_logical;
 };
 
 inline Grid make_grid(const FwdParams &f) {
@@ -46,7 +46,7 @@ inline Grid make_grid(const FwdParams &f) {
     g.n_tt = (f.N + TT - 1) / TT;
     g.n_hg = (f.H + HG - 1) / HG;
     while (g.n_hg < f.H && (int64_t)f.B * g.n_tt * g.n_hg < 2048) ++g.n_hg;
-    g.n_logical = (int64_t)f.B * g.n_tt * g.n_hg;
+    g.n_logical = (uint32_t)((int64_t)f.B * g.n_tt * g.n_hg);
     return g;
 }
 
@@ -59,11 +59,10 @@ __global__ __launch_bounds__(NT) void smallk_bwd_q_kernel(BwdParams bp, Grid gd)
     constexpr int E = BD::E, CPR = BD::CPR, ROWB = BD::ROWB;
     const FwdParams &p = bp.f;
     __shared__ alignas(16) unsigned char band[2][2][BD::ROWS * ROWB];   // [buffer][K, V]
-    const int64_t logical = xcd_remap(blockIdx.x, gd.n_logical);
-    if (logical < 0) return;
-    const int hg = (int)(logical % gd.n_hg);
-    const int tt = (int)((logical / gd.n_hg) % gd.n_tt);
-    const int b = (int)(logical / ((int64_t)gd.n_hg * gd.n_tt));
+    const uint32_t logical = xcd_remap(blockIdx.x, gd.n_logical);
+    if (logical >= gd.n_logical) return;
+    const DivMod group_of = divmod(logical, gd.n_hg), tile_of = divmod(group_of.quot, gd.n_tt);
+    const int hg = (int)group_of.rem, tt = (int)tile_of.rem, b = (int)tile_of.quot;
     const int N = p.N, kw = p.k, pi = p.pi;
     const int hpg = (p.H + gd.n_hg - 1) / gd.n_hg;
     const int h0 = hg * hpg, h1 = min(p.H, h0 + hpg);
@@ -231,11 +230,10 @@ __global__ __launch_bounds__(NT) void smallk_bwd_kv_kernel(BwdParams bp, Grid gd
     const FwdParams &p = bp.f;
     __shared__ alignas(16) unsigned char band[2][2][BD::ROWS * ROWB];   // [buffer][Q, dL/dy]
     __shared__ float rowf[2][4][BD::ROWS];   // [buffer][lse2, r, local bias2, partner bias2]
-    const int64_t logical = xcd_remap(blockIdx.x, gd.n_logical);
-    if (logical < 0) return;
-    const int hg = (int)(logical % gd.n_hg);
-    const int tt = (int)((logical / gd.n_hg) % gd.n_tt);
-    const int b = (int)(logical / ((int64_t)gd.n_hg * gd.n_tt));
+    const uint32_t logical = xcd_remap(blockIdx.x, gd.n_logical);
+    if (logical >= gd.n_logical) return;
+    const DivMod group_of = divmod(logical, gd.n_hg), tile_of = divmod(group_of.quot, gd.n_tt);
+    const int hg = (int)group_of.rem, tt = (int)tile_of.rem, b = (int)tile_of.quot;
     const int N = p.N, kw = p.k, pi = p.pi;
     const int hpg = (p.H + gd.n_hg - 1) / gd.n_hg;
     const int h0 = hg * hpg, h1 = min(p.H, h0 + hpg);

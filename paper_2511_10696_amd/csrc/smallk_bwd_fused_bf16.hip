@@ -55,7 +55,7 @@ struct Ring {
 
 struct Runs {
     int len, n;          // rows per run, runs per (b, h)
-    int64_t n_logical;
+    uint32_t n_logical;
 };
 
 // x or x - n, for x in [0, 2 n)
@@ -74,14 +74,15 @@ __global__ __launch_bounds__(NT, BIDIR ? 3 : 4) void smallk_bwd_fused_kernel(Bwd
     __shared__ float2 rs[R::ROWS];                            // lse, gate logit
     __shared__ alignas(8) unsigned char we[WBYTES];           // (alpha^, ddelta) of queries [s - BACK, s + 32)
 
-    const int64_t logical = xcd_remap(blockIdx.x, runs.n_logical);
-    if (logical < 0) return;
-    const int64_t bh = logical / runs.n;
-    const int h = (int)(bh % p.H), b = (int)(bh / p.H);
+    const uint32_t logical = xcd_remap(blockIdx.x, runs.n_logical);
+    if (logical >= runs.n_logical) return;
+    const DivMod run_of = divmod(logical, runs.n), head_of = divmod(run_of.quot, p.H);
+    const int64_t bh = run_of.quot;
+    const int h = (int)head_of.rem, b = (int)head_of.quot;
     const int N = p.N, kw = p.k, pi = p.pi;
     const bool par = partner_enabled(kw, pi);
     const int reach = par ? pi : kw;
-    const int c0 = (int)(logical % runs.n) * runs.len, c1 = min(N, c0 + runs.len);
+    const int c0 = (int)run_of.rem * runs.len, c1 = min(N, c0 + runs.len);
     const int tid = threadIdx.x;
     const int i = tid >> 3, sl = tid & 7;   // row of the step, lane within its row
     const int nw = BIDIR ? 2 * kw + 1 : kw + 1;
@@ -261,7 +262,7 @@ hipError_t launch_k(const BwdParams &p, hipStream_t stream) {
     const int64_t n = std::max<int64_t>(1, std::min<int64_t>((want + bh - 1) / bh, (p.f.N + 127) / 128));
     runs.len = (int)((((int64_t)p.f.N + n - 1) / n + STEP - 1) / STEP * STEP);
     runs.n = (p.f.N + runs.len - 1) / runs.len;
-    runs.n_logical = bh * runs.n;
+    runs.n_logical = (uint32_t)(bh * runs.n);
     return launch_kernel(smallk_bwd_fused_kernel<BIDIR, KMAX>, dim3((unsigned)xcd_grid(runs.n_logical)), dim3(NT),
                          stream, p, runs);
 }
