@@ -102,11 +102,24 @@ __device__ inline float col_max(float x) {
     return fmaxf(x, __shfl_xor(x, 32));
 }
 
+template <int D>
+__device__ inline void mma_rows(Acc<D> &acc, const ColFrag<D> &f, const float (&w)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                acc.a[4 * h + e] =
+                    __builtin_amdgcn_mfma_f32_16x16x4f32(f.x[i][h][e], w[i], acc.a[4 * h + e], 0, 0, 0);
+}
+
 // acc[column] += sum over the block's rows of w[row] * row, for the entries
-// that are in the working set.  w is 0 for the others, but 0 times a row
+// that are in the working set.  w is 0 for the others, but 0 times an element
 // that is not finite is not: a block that has such entries (`edge`) is
-// checked for elements that are not finite and, if there are any, summed
-// entry by entry over the valid ones (`ok`: bit i for slot i).
+// checked for them and, if there are any, they are added entry by entry over
+// the valid ones (`ok`: bit i for slot i) and enter the product as 0, so that
+// a column whose working set has none of them keeps its bits.
 template <int D, typename RowPtr>
 __device__ inline void add_rows(Acc<D> &acc, const ColFrag<D> &f, const float (&w)[4], bool edge, unsigned ok,
                                 RowPtr row, int lane) {
@@ -137,21 +150,25 @@ __device__ inline void add_rows(Acc<D> &acc, const ColFrag<D> &f, const float (&
                     for (int r = 0; r < 4; ++r) {
                         const f32x4 v = *reinterpret_cast<const f32x4 *>(p + 64 * h + 4 * r);
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            acc.a[4 * h + e][r] = in ? __builtin_fmaf(wj, v[e], acc.a[4 * h + e][r]) : acc.a[4 * h + e][r];
+                        for (int e = 0; e < 4; ++e) {
+                            const float a = acc.a[4 * h + e][r];
+                            acc.a[4 * h + e][r] = in && !(fabsf(v[e]) < INFINITY) ? __builtin_fmaf(wj, v[e], a) : a;
+                        }
                     }
             }
+            ColFrag<D> x;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        x.x[i][h][e] = fabsf(f.x[i][h][e]) < INFINITY ? f.x[i][h][e] : 0.0f;
+            mma_rows<D>(acc, x, w);
             return;
         }
     }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int h = 0; h < D / 64; ++h)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                acc.a[4 * h + e] =
-                    __builtin_amdgcn_mfma_f32_16x16x4f32(f.x[i][h][e], w[i], acc.a[4 * h + e], 0, 0, 0);
+    mma_rows<D>(acc, f, w);
 }
 
 // Column c's row of the accumulator, times f, to dst (the row's first element).

@@ -45,7 +45,7 @@ def test_f32_tiles(device, B, H, N, D, k, pi, causal, pq):
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")])
 def test_f32_rows_not_finite(device, causal, H, bad):
     """A key, value, query or dL/dy row that is not finite reaches exactly the
-    rows whose working sets meet it."""
+    rows whose working sets meet it; the others keep their bits."""
     B, N, D, k, pi, x = 1, 300, 64, 21, 50, 120
     cfg = W.ForwardConfig("custom", B, H, N, D, k, pi, torch.float32)
     q, kk, v, gate = W.forward_inputs(cfg, 12, device)
@@ -58,8 +58,7 @@ def test_f32_rows_not_finite(device, causal, H, bad):
     clean = pa.pi_attn_backward(q, kk, v, gate, k, pi, out, lse, do, gate_grad_per_query=True, causal=causal)
 
     def same_but(got, ref, rows):
-        assert torch.isfinite(got[:, :, ~rows]).all()
-        assert (got[:, :, ~rows] - ref[:, :, ~rows]).abs().max() <= 1e-4 * max(1.0, ref.abs().max().item())
+        assert torch.equal(got[:, :, ~rows], ref[:, :, ~rows])
 
     def poison(t):
         p = t.clone()
