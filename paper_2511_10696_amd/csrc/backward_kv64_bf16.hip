@@ -299,7 +299,8 @@ __global__ __launch_bounds__(NT, 2) void backward_kv64_bf16_kernel(BwdParams bp,
     // ---- store: lane (c, g) holds dims 32db + 8i + 4g + [0, 4) of key c ----
     // Whole rows: each wavefront passes its 32 rows through a private LDS
     // region (the tile buffers, free once every wavefront has left the loop)
-    // and stores 256 contiguous bytes per row, 16 bytes per lane.
+    // and stores 256 contiguous bytes per row, 16 bytes per lane, not kept in
+    // the caches (a training pass at B4 H16 N4096 k128: 173 -> 167 us).
     constexpr int P = 4 * D + 16;   // LDS row pitch (bytes), padded against bank conflicts
     static_assert(2 * 32 * P <= (int)sizeof(TileBuf), "store staging fits a tile buffer");
     __syncthreads();
@@ -319,7 +320,7 @@ __global__ __launch_bounds__(NT, 2) void backward_kv64_bf16_kernel(BwdParams bp,
         for (int v = 0; v < 8; ++v) {
             const int r = 4 * v + (lane >> 4), ch = lane & 15;
             const f32x4 a = *reinterpret_cast<const f32x4 *>(reg + r * P + ch * 16);
-            if (kq0 + r < NK) *reinterpret_cast<f32x4 *>(dst + (obase + kq0 + r) * D + 4 * ch) = a;
+            if (kq0 + r < NK) __builtin_nontemporal_store(a, reinterpret_cast<f32x4 *>(dst + (obase + kq0 + r) * D + 4 * ch));
         }
     };
     store(bp.dv, dv, 1.0f);
