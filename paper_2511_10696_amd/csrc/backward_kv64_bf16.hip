@@ -95,8 +95,9 @@ __global__ __launch_bounds__(NT, 2) void backward_kv64_bf16_kernel(BwdParams bp,
     const int ntiles = band_hi > band_lo ? (band_hi - band_lo + TK - 1) / TK : 0;
     const int b0 = max(band_lo, QS);
     const int rowq = (int)(2 * sn), rowo = (int)(2 * osn);
-    const u32x4 rq = raw_rsrc(qp + (int64_t)b0 * sn, (band_hi - b0) * rowq);
-    const u32x4 ro = raw_rsrc(op + (int64_t)b0 * osn, (band_hi - b0) * rowo);
+    // up to the last row's end (row strides may be 0)
+    const u32x4 rq = raw_rsrc(qp + (int64_t)b0 * sn, (band_hi - b0 - 1) * rowq + 2 * D);
+    const u32x4 ro = raw_rsrc(op + (int64_t)b0 * osn, (band_hi - b0 - 1) * rowo + 2 * D);
     auto fetch = [&](TileBuf &tb, int m) __attribute__((always_inline)) {
         const int row0 = band_lo + TK * m - b0;
         fetch_tile<D, BIDIR>(tb.q, rq, rowq, row0, w, lane);

@@ -32,3 +32,18 @@ def test_rows_stored_alike(device, D, N, k, pi, causal, strided):
         for i in (0, times - 1):
             assert torch.equal(got[0][:, H * i:H * (i + 1)], few)
             assert not with_lse or torch.equal(got[1][:, H * i:H * (i + 1)], lse)
+
+
+def test_shard_queries_and_gradients_of_stride_zero(device):
+    """Query (and dL/dy) rows of a shard call that are one row, repeated."""
+    H, N, D, k, pi = 130, 300, 64, 40, 100
+    cfg = W.ForwardConfig("custom", 1, H, N, D, k, pi, torch.bfloat16)
+    q, kk, v, gate = W.forward_inputs(cfg, 62, device, per_query_gate=True)
+    q0, do0 = (x[:, :, :1].expand(1, H, N, D) for x in (q, W.cotangent(q.shape, q.dtype, 62, device)))
+    call = lambda x: pa.pi_attn_forward_shard(x, kk, v, gate, k, pi, N, 0, 0, return_lse=True)
+    (out, lse), (ref, rlse) = call(q0), call(q0.contiguous())
+    assert torch.equal(out, ref) and torch.equal(lse, rlse)
+    rt = torch.rand((1, H, N), device="cuda")
+    back = lambda x, d: pa.pi_attn_backward_shard_kv(x, kk, v, gate, k, pi, N, 0, 0, lse, rt, d)
+    for a, b in zip(back(q0, do0), back(q0.contiguous(), do0.contiguous())):
+        assert torch.equal(a, b)
