@@ -297,9 +297,29 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void forward_bf16_kernel(FwdPa
     // partner zero the data afterwards.
     W ws;
     const int tq = t_ok ? t : p.qpos0;
+    // The query rows.  D = 64: fetched whole into this wavefront's part of the
+    // second tile buffer (free until the first barrier) in the key tile's
+    // layout, rows past the last query as zeros: eight 128-byte lines an
+    // instruction instead of 32 bytes of each of 32 rows (36.5 -> 35.9 us at
+    // B4 H16 N4096 k128, 39.2 -> 38.3 us bidirectionally at B8 H12 N2000, 8.3
+    // -> 8.1 us at B1 H16 N1000; no gain at D = 128).
+    constexpr bool QLDS = D == 64;
     bf16x8 qraw[W::KS];
+    unsigned char *qreg = reinterpret_cast<unsigned char *>(&tB) + w * 32 * T::ROW_BYTES;
+    if constexpr (QLDS) {
+        static_assert(WAVES * 32 * T::ROW_BYTES <= (int)sizeof(TileBuf<D>), "the query rows fit a tile buffer");
+        const int rowbq = (int)(2 * sn);
+        const u32x4 rq = raw_rsrc(qp + (int64_t)min(q0, NQ - 1) * sn,
+                                  q0 < NQ ? (min(32, NQ - q0) - 1) * rowbq + T::ROW_BYTES : 0);
 #pragma unroll
-    for (int s = 0; s < W::KS; ++s) qraw[s] = *reinterpret_cast<const bf16x8 *>(qp + tq * sn + 16 * s + 8 * g);
+        for (int u = 0; u < 32 * T::CPR / 64; ++u) {
+            const int pidx = 64 * u + lane, row = pidx / T::CPR, pc = pidx % T::CPR;
+            lds_fetch16(rq, row * rowbq + k_swz(row, pc, T::CPR) * 16, qreg + 1024 * u);
+        }
+    } else {
+#pragma unroll
+        for (int s = 0; s < W::KS; ++s) qraw[s] = *reinterpret_cast<const bf16x8 *>(qp + tq * sn + 16 * s + 8 * g);
+    }
     const float gl = p.gate[b * p.gsb + h * p.gsh + (tq - p.qpos0) * p.gsn];
 
     // Partner rows: A-operand row c of the wavefront is row q0 + c - pi, the
@@ -333,8 +353,16 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void forward_bf16_kernel(FwdPa
         }
     }
     if (ntiles > 0) tile_fetch<D>(tA, rk, rv, rowb, 0, w, lane);
+    if constexpr (QLDS) {
+        __builtin_amdgcn_s_waitcnt(0xF70);   // vmcnt(0): this wavefront's own fetches, read by itself alone
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 #pragma unroll
-    for (int s = 0; s < W::KS; ++s) ws.qf[s] = t_ok ? qraw[s] : bf16x8{};
+        for (int s = 0; s < W::KS; ++s)
+            ws.qf[s] = *reinterpret_cast<const bf16x8 *>(qreg + c * T::ROW_BYTES + k_swz(c, 2 * s + g, T::CPR) * 16);
+    } else {
+#pragma unroll
+        for (int s = 0; s < W::KS; ++s) ws.qf[s] = t_ok ? qraw[s] : bf16x8{};
+    }
 
     const FusionBias fb = fusion_bias(gl, CLAMP);
     const float c2 = p.scale * kLog2e;
