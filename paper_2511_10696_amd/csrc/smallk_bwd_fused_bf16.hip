@@ -23,7 +23,7 @@
 // read about once: 1.35 GB at B8 H16 N8192); at k = 8 and bidirectionally the
 // VALU, 84 instructions an entry and 8 rows.  Against the two passes: 400 ->
 // 266 us at B8 H16 N8192 k4 pi16, 457 -> 320 us at k8, bidirectional 503 ->
-// 362 us and 706 -> 549 us; B4 H8 N2000 38 -> 31 us.  With the sums of the two
+// 357 us and 706 -> 549 us; B4 H8 N2000 38 -> 31 us.  With the sums of the two
 // passes (dq = sum w dP k - r sum w k) in place of kept alpha^ and dP, a ring
 // of three and four steps and two barriers a step: 309 and 153 us where this
 // takes 300 and 100 (causal B8 H16 N8192, bidirectional B32 H8 N1000).
@@ -39,6 +39,8 @@ namespace pi_attn {
 namespace {
 
 using namespace sk;
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int D = 64;
 constexpr int STEP = 32;        // rows per step
@@ -72,6 +74,9 @@ __global__ __launch_bounds__(NT, BIDIR ? 3 : 4) void smallk_bwd_fused_kernel(Bwd
     const FwdParams &p = bp.f;
     __shared__ alignas(16) unsigned char ring[4][R::BYTES];   // q, k, v, dL/dy
     __shared__ float2 rs[R::ROWS];                            // lse, gate logit
+    // Whole rows of gradients, half a row at a time (see store_row).
+    constexpr bool WHOLE = BIDIR && KMAX == 4;
+    __shared__ alignas(16) float stage[WHOLE ? NT / 64 : 1][8][32];
     __shared__ alignas(8) unsigned char we[WBYTES];           // (alpha^, ddelta) of queries [s - BACK, s + 32)
 
     const uint32_t logical = xcd_remap(blockIdx.x, runs.n_logical);
@@ -126,6 +131,33 @@ __global__ __launch_bounds__(NT, BIDIR ? 3 : 4) void smallk_bwd_fused_kernel(Bwd
         if (sl == 0) rs[slot] = make_float2(r.lse, r.gl);
     };
     auto chunk = [&](int tensor, int off) { return *reinterpret_cast<const uint4 *>(ring[tensor] + off); };
+
+    // A row of a gradient, times f, where `ok`.  As it lies a lane stores 32
+    // bytes in two pieces.  WHOLE: the wavefront's 8 rows go through LDS, half
+    // a row at a time, and out as whole 128-byte lines that are not kept in
+    // the caches: 152.8 -> 145.7 us a training pass at B32 H8 N1000
+    // bidirectionally; causal k = 4, at the copy rate either way, 425 -> 428
+    // us; at k = 8 the LDS it takes costs a work-group per CU.
+    auto store_row = [&](float *dst, const float (&v)[8], float f, bool ok) __attribute__((always_inline)) {
+        const f32x4 lo = {v[0] * f, v[1] * f, v[2] * f, v[3] * f}, hi = {v[4] * f, v[5] * f, v[6] * f, v[7] * f};
+        if constexpr (WHOLE) {
+            float *reg = &stage[tid >> 6][i & 7][0];
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                __builtin_amdgcn_wave_barrier();
+                if ((sl >> 2) == half) {
+                    *reinterpret_cast<f32x4 *>(reg + 8 * (sl & 3)) = lo;
+                    *reinterpret_cast<f32x4 *>(reg + 8 * (sl & 3) + 4) = hi;
+                }
+                __builtin_amdgcn_wave_barrier();
+                const f32x4 x = *reinterpret_cast<const f32x4 *>(reg + 4 * sl);
+                if (ok) __builtin_nontemporal_store(x, reinterpret_cast<f32x4 *>(dst + 32 * half + 4 * sl));
+            }
+        } else if (ok) {
+            *reinterpret_cast<f32x4 *>(dst + 8 * sl) = lo;
+            *reinterpret_cast<f32x4 *>(dst + 8 * sl + 4) = hi;
+        }
+    };
 
     // ring slot of row s - BACK, and the weights' of query s - BACK (bytes)
     int os = 0, ws = 0;
@@ -195,23 +227,19 @@ __global__ __launch_bounds__(NT, BIDIR ? 3 : 4) void smallk_bwd_fused_kernel(Bwd
             for (int x = 0; x < NW; ++x) {
                 if (x < nw) add(NP + x, at(x - kw), d_loc);
             }
-            if (t >= c0 && t < c1) {
-                float *dqp = bp.dq + (rbase + t) * D + 8 * sl;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) dq[e] *= p.scale;
-                *reinterpret_cast<float4 *>(dqp) = make_float4(dq[0], dq[1], dq[2], dq[3]);
-                *reinterpret_cast<float4 *>(dqp + 4) = make_float4(dq[4], dq[5], dq[6], dq[7]);
-                if (sl == 0) {
-                    bp.dgate[rbase + t] = d_loc * gdv.local + d_par * gdv.partner;
-                    bp.rowterm[rbase + t] = r;
-                }
+            const bool mine = t >= c0 && t < c1;
+            store_row(bp.dq + (rbase + t) * D, dq, p.scale, mine);
+            if (mine && sl == 0) {
+                bp.dgate[rbase + t] = d_loc * gdv.local + d_par * gdv.partner;
+                bp.rowterm[rbase + t] = r;
             }
         }
         __syncthreads();   // the weights are in place
 
         // ---- keys --------------------------------------------------------------
         const int j = t - reach;
-        if (j >= c0 && j < c1) {
+        const bool mine = j >= c0 && j < c1;
+        if (WHOLE || mine) {
             float dk[8], dv[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) dk[e] = dv[e] = 0.0f;
@@ -233,13 +261,8 @@ __global__ __launch_bounds__(NT, BIDIR ? 3 : 4) void smallk_bwd_fused_kernel(Bwd
                 const int d = x - (BIDIR ? kw : 0);
                 if (x < nw) visit(d, NP + kw - d);
             }
-            float *dkp = bp.dk + (rbase + j) * D + 8 * sl, *dvp = bp.dv + (rbase + j) * D + 8 * sl;
-            *reinterpret_cast<float4 *>(dkp) =
-                make_float4(dk[0] * p.scale, dk[1] * p.scale, dk[2] * p.scale, dk[3] * p.scale);
-            *reinterpret_cast<float4 *>(dkp + 4) =
-                make_float4(dk[4] * p.scale, dk[5] * p.scale, dk[6] * p.scale, dk[7] * p.scale);
-            *reinterpret_cast<float4 *>(dvp) = make_float4(dv[0], dv[1], dv[2], dv[3]);
-            *reinterpret_cast<float4 *>(dvp + 4) = make_float4(dv[4], dv[5], dv[6], dv[7]);
+            store_row(bp.dk + (rbase + j) * D, dk, p.scale, mine);
+            store_row(bp.dv + (rbase + j) * D, dv, 1.0f, mine);
         }
         if (n + 1 == steps) break;
         __syncthreads();   // rows [s - BACK, s) are done with
