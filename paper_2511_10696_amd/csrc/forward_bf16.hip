@@ -250,17 +250,25 @@ __device__ inline void softmax_block(Wave<D> &ws, f32x16 &s, bool edge, int j0, 
     ws.lb = sum_bf16x8(pb[1], sum_bf16x8(pb[0], ws.lb));
 }
 
-template <int D, bool CLAMP, bool BIDIR, bool LSE>
-__global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void forward_bf16_kernel(FwdParams p, int n_qt, uint32_t n_logical,
-                                                                               bool whole_rows) {
+template <int D, bool CLAMP, bool BIDIR, bool LSE, bool FULL>
+__global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void forward_bf16_kernel(FwdParams p, int n_qt, uint32_t n_logical) {
     using T = Tile<D>;
     using W = Wave<D>;
     __shared__ TileBuf<D> tA, tB;
     const uint32_t logical = xcd_remap(blockIdx.x, n_logical);
     if (logical >= n_logical) return;
-    const DivMod tile_of = divmod(logical, n_qt), head_of = divmod(tile_of.quot, p.H);
-    const int qt = (int)tile_of.rem, h = (int)head_of.rem, b = (int)head_of.quot;
-    const int64_t bh = tile_of.quot;
+    // Order: the tiles of a head one after the other (they share most of their
+    // keys), or, at D = 64 in launches that fill the chip (FULL), the heads of
+    // a tile: 36.2 -> 34.4 us at B4 H16 N4096 k128, 39.5 -> 34.7 us
+    // bidirectionally at B8 H12 N2000 ([B][N][H][D] storage), equal at k = 512;
+    // D = 128 loses (B1 H32 N32768 k512 487 -> 547 us: its band is read from
+    // HBM again), and so do small launches (8.1 -> 8.3 us at B1 H16 N1000, the
+    // same for the choice made at run time).  With the lse a backward follows,
+    // which starts on the tiles of a head: a training pass at the first shape
+    // takes 166.6 us in that order and 167.6 us in the other.
+    const Order o = tile_order<FULL && D == 64 && !LSE>(logical, n_qt, p.H);
+    const int qt = o.tile, h = o.h, b = o.b;
+    const int64_t bh = o.bh;
 
     const int tid = threadIdx.x;
     const int lane = __lane_id();
@@ -533,7 +541,7 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void forward_bf16_kernel(FwdPa
     // ---- normalise and store -----------------------------------------------
     // Lane (c, g) holds dims 32db + 8i + 4g + [0, 4) of query c: stored as they
     // lie, an instruction writes 16 bytes of each of 32 rows.  Launches that
-    // fill the chip (whole_rows) pass each wavefront's rows through a private
+    // fill the chip (FULL) pass each wavefront's rows through a private
     // LDS region and store whole rows, 16 bytes per lane, not kept in the
     // caches: 43.1 -> 37.5 us at B4 H16 N4096 D64 k128 and 43.4 -> 39.5 us
     // bidirectionally at B8 H12 N2000, equal at D = 128; stores as they lie
@@ -549,7 +557,7 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void forward_bf16_kernel(FwdPa
         for (int j = 0; j < 4; ++j) o4[j] = (__bf16)(ws.o[db][4 * i + j] * inv);
         return o4;
     };
-    if (whole_rows) {
+    if constexpr (FULL) {
         constexpr int P = 2 * D + 16;                     // LDS row pitch (bytes), padded against bank conflicts
         constexpr int LPR = D / 8, RPI = 64 / LPR;        // lanes per row, rows per instruction
         static_assert(2 * 32 * P <= (int)sizeof(TileBuf<D>), "store staging fits a tile buffer");
@@ -586,9 +594,10 @@ hipError_t launch(const FwdParams &p, hipStream_t stream) {
     const int64_t n_logical = (int64_t)p.B * p.H * n_qt;
     if (n_logical == 0) return hipSuccess;
     const int64_t grid = xcd_grid(n_logical);
-    const bool whole_rows = n_logical >= 1024;   // four work-groups per CU at D = 64
-    return launch_kernel(forward_bf16_kernel<D, CLAMP, BIDIR, LSE>, dim3((unsigned)grid), dim3(NT), stream, p, n_qt,
-                         (uint32_t)n_logical, whole_rows);
+    const bool full = n_logical >= 1024;   // four work-groups per CU at D = 64
+    return launch_kernel(full ? forward_bf16_kernel<D, CLAMP, BIDIR, LSE, true>
+                              : forward_bf16_kernel<D, CLAMP, BIDIR, LSE, false>,
+                         dim3((unsigned)grid), dim3(NT), stream, p, n_qt, (uint32_t)n_logical);
 }
 
 template <int D, bool BIDIR, bool LSE>

@@ -118,6 +118,21 @@ __device__ inline DivMod divmod(uint32_t x, uint32_t d) {
     return DivMod{q, x - q * d};
 }
 
+// Tile and head of a logical index over B x H x n_tiles: the tiles of a head
+// one after the other, or (HEADS) the heads of a tile.
+struct Order {
+    int tile, h, b;
+    int64_t bh;
+};
+
+template <bool HEADS>
+__device__ inline Order tile_order(uint32_t logical, int n_tiles, int H) {
+    const DivMod inner = divmod(logical, HEADS ? H : n_tiles), outer = divmod(inner.quot, HEADS ? n_tiles : H);
+    const uint32_t h = HEADS ? inner.rem : outer.rem;
+    return Order{(int)(HEADS ? outer.rem : inner.rem), (int)h, (int)outer.quot,
+                 HEADS ? outer.quot * H + h : inner.quot};
+}
+
 // ---- direct global-to-LDS tile fetch ---------------------------------------
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
