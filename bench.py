@@ -55,9 +55,11 @@ SMALLK_TRAFFIC = {"gated": os.path.join(ROOT, "profiles", "smallk_bf16_gated_sma
                                                          "smallk_bwd_bf16_bidir_smallk8k_counters.txt")}
 FORWARD_SOURCES = ("forward_bf16.hip", "pi_common.h", "kernels.h")
 SMALLK_SOURCES = ("smallk_bf16.hip", "smallk_common.h", "smallk.h", "pi_common.h", "kernels.h")
-SMALLK_BWD_SOURCES = ("smallk_bwd_bf16.hip", "smallk_common.h", "smallk.h", "backward.hip", "pi_common.h",
-                      "kernels.h")
-BACKWARD_SOURCES = ("backward_bf16.hip", "backward_kv_bf16.hip", "backward.hip", "pi_common.h", "kernels.h")
+SMALLK_BWD_SOURCES = ("smallk_bwd_fused_bf16.hip", "smallk_bwd_bf16.hip", "smallk_common.h", "smallk.h",
+                      "backward.hip", "pi_common.h", "kernels.h")
+BACKWARD_SOURCES = ("backward_bf16.hip", "backward_kv_bf16.hip", "bwd_tile.h", "backward.hip", "pi_common.h",
+                    "kernels.h")
+DECODE_SOURCES = ("decode.hip", "pi_common.h", "kernels.h")
 
 
 def csrc_digest(names):
@@ -393,7 +395,7 @@ def main():
                                   args.cold_reps, stream)
     keys, flops, nbytes = forward_algorithmic(cfg)
     digest = csrc_digest(FORWARD_SOURCES)
-    roofline, roofline_mfma = roofline_of(flops, nbytes, sec, "forward_bf16_kernel<128,false,false,false>",
+    roofline, roofline_mfma = roofline_of(flops, nbytes, sec, "forward_bf16_kernel<128,false,false,false,true>",
                                           measured_traffic(digest), measured_counters(digest, PROFILE_TRAFFIC, sec))
     host_inputs = [x.cpu() for x in (q, k, v, gate)]   # the exact bytes the kernel consumed, for the CPU baseline
 
@@ -404,7 +406,7 @@ def main():
             torch, lambda: pa.pi_attn_forward(q, k, v, gate, cfg.k, cfg.pi, out=out, causal=False),
             args.steps, args.warmup, stream)
         bkeys, bflops, bbytes = forward_algorithmic(cfg, causal=False)
-        brl, bmf = roofline_of(bflops, bbytes, bms / 1e3, "forward_bf16_kernel<128,false,true,false>",
+        brl, bmf = roofline_of(bflops, bbytes, bms / 1e3, "forward_bf16_kernel<128,false,true,false,true>",
                                measured_traffic(digest, BIDIR_TRAFFIC),
                                measured_counters(digest, BIDIR_TRAFFIC, bms / 1e3))
         bidir = {"workload": "fwd32k bidirectional: B1 H32 N32768 D128 k512 pi1024 bf16 (window |j-t|<=k, "
@@ -423,7 +425,7 @@ def main():
             vms, _, _ = time_launches(torch, lambda: pa.pi_attn_forward(q, k, v, gate, kk, pp, out=out), steps,
                                       1, stream)
             vkeys, vflops, vbytes = forward_algorithmic(vcfg)
-            vrl, vmf = roofline_of(vflops, vbytes, vms / 1e3, "forward_bf16_kernel<128,false,false,false>")
+            vrl, vmf = roofline_of(vflops, vbytes, vms / 1e3, "forward_bf16_kernel<128,false,false,false,true>")
             variants[name] = {"workload": f"fwd32k shape, causal, k={kk} pi={pp}", "steps": steps,
                               "ms_per_step": round(vms, 5),
                               "query_positions_per_s": round(cfg.B * cfg.N / (vms / 1e3), 1),
@@ -440,7 +442,7 @@ def main():
             cms, _, _ = time_launches(torch, cfn, args.steps, args.warmup, stream)
             ccold, ccold_min = time_cold(torch, cfn, args.cold_reps, stream)
             ckeys, cflops, cbytes = forward_algorithmic(ccfg)
-            crl, cmf = roofline_of(cflops, cbytes, cms / 1e3, f"forward_bf16_kernel<{ccfg.D},false,false,false>")
+            crl, cmf = roofline_of(cflops, cbytes, cms / 1e3, f"forward_bf16_kernel<{ccfg.D},false,false,false,true>")
             variants[cname] = {"workload": f"{cname}: causal B{ccfg.B} H{ccfg.H} N{ccfg.N} D{ccfg.D} k{ccfg.k} "
                                            f"pi{ccfg.pi} bf16", "steps": args.steps, "ms_per_step": round(cms, 5),
                                "query_positions_per_s": round(ccfg.B * ccfg.N / (cms / 1e3), 1),
@@ -508,8 +510,7 @@ def main():
         torch.cuda.synchronize()
         per = sorted(ev[i].elapsed_time(ev[i + 1]) for i in range(nsteps))
         dkeys, dbytes = decode_algorithmic(dcfg, dcfg.cache_len)
-        ddigest = source_digest([os.path.join(ROOT, "paper_2511_10696_amd", "csrc", f)
-                                 for f in ("decode.hip", "pi_common.h", "kernels.h")])
+        ddigest = csrc_digest(DECODE_SOURCES)
         dtraffic = measured_traffic(ddigest, DECODE_TRAFFIC)
         dcounters = measured_counters(ddigest, DECODE_TRAFFIC, dms / 1e3)
         dgbs = dbytes / (dms / 1e3) / 1e9
@@ -610,7 +611,7 @@ def bench_smallk(W, pa, torch, dev, stream, steps, warmup):
         keys, flops, nbytes = backward_algorithmic(cfg, causal)
         mode = "false" if causal else "true"
         rl, _ = roofline_of(flops, nbytes, ms / 1e3,
-                            f"smallk_bwd_q_kernel<64,{mode},4> + smallk_bwd_kv_kernel<64,{mode},4>",
+                            f"smallk_bwd_fused_kernel<{mode},4>",
                             measured_traffic(csrc_digest(SMALLK_BWD_SOURCES), SMALLK_TRAFFIC[name]),
                             measured_counters(csrc_digest(SMALLK_BWD_SOURCES), SMALLK_TRAFFIC[name], ms / 1e3))
         res[name] = {"us_per_step": round(ms * 1e3, 2),
@@ -642,7 +643,7 @@ def bench_shard(cfg, W, pa, torch, dev, stream, steps, warmup, nshard=8, rank=6)
         torch, lambda: pa.pi_attn_forward_shard(qs, ks, vs, gate, cfg.k, cfg.pi, n, s0, lo, out=out),
         steps, warmup, stream)
     keys, flops, nbytes = shard_algorithmic(cfg, s0, s1, lo)
-    rl, mf = roofline_of(flops, nbytes, ms / 1e3, "forward_bf16_kernel<128,false,false,false> (one shard)")
+    rl, mf = roofline_of(flops, nbytes, ms / 1e3, "forward_bf16_kernel<128,false,false,false,true> (one shard)")
     res = {"workload": (f"fwd32k sequence-sharded {nshard} ways, rank {rank}'s share: queries [{s0}, {s1}), "
                         f"k/v rows [{lo}, {s1}) (its own and the pi = {cfg.pi} halo rows), B1 H32 D128 k512"),
            "steps": steps, "us_per_step": round(ms * 1e3, 2),
