@@ -187,10 +187,13 @@ __global__ __launch_bounds__(NT, BIDIR ? 3 : 4) void smallk_bwd_fused_kernel(Bwd
             const float2 sv = rs[wrap(os + BACK + i, R::ROWS)];
             const FusionBias fb = fusion_bias(sv.y, clamp_on);
             const GateDeriv gdv = gate_deriv(sv.y);
-            // weights of a query outside the sequence are 0
-            const float lse2 = t_ok ? (sv.x - fb.lse_shift) * kLog2e : INFINITY;
-            float al[NE], ds[NE], r = 0.0f;   // alpha^, dP and then ddelta
-            unsigned cuts = 0;
+            const float lse2 = (sv.x - fb.lse_shift) * kLog2e;
+            float al[NE], ds[NE], r = 0.0f;   // alpha^, dP
+            // A query outside the sequence has no entries: alpha^ and ddelta
+            // are 0 whatever the rows around it hold (0 times a row that is
+            // not finite would reach keys that no query of that row's has).
+            unsigned cuts = t_ok ? 0u : ~0u;
+            const unsigned rows = t_ok ? N : 0;
             auto score = [&](int e, int off, bool ok, float bias) __attribute__((always_inline)) {
                 bool cut;
                 const float s2 = logit2(sum8(dot8(qc, chunk(1, off), 0.0f)), bias, p, clamp_on, cut);
@@ -202,12 +205,12 @@ __global__ __launch_bounds__(NT, BIDIR ? 3 : 4) void smallk_bwd_fused_kernel(Bwd
             // offset of row t + d (a row outside the sequence is zeros)
             auto at = [&](int d) { return wrap(tb + d * ROWB, R::BYTES); };
             if (par) {
-                score(0, at(-pi), t >= pi, fb.partner);
-                if constexpr (BIDIR) score(1, at(pi), pi < N - t, fb.partner);
+                score(0, at(-pi), (unsigned)t - pi < rows, fb.partner);
+                if constexpr (BIDIR) score(1, at(pi), (unsigned)t + pi < rows, fb.partner);
             }
 #pragma unroll
             for (int x = 0; x < NW; ++x) {
-                if (x < nw) score(NP + x, at(x - kw), t - kw + x >= 0 && (!BIDIR || t - kw + x < N), fb.local);
+                if (x < nw) score(NP + x, at(x - kw), (unsigned)t - kw + x < rows, fb.local);
             }
             float dq[8], d_par = 0.0f, d_loc = 0.0f;
 #pragma unroll

@@ -57,9 +57,12 @@ def test_against_the_oracle(device, causal, k, pi):
 
 
 @pytest.mark.parametrize("causal", [True, False])
-def test_rows_not_finite(device, causal):
-    """A row that is not finite reaches the rows whose working sets meet it."""
-    N, k, pi, x, times = 600, 4, 16, 250, 41
+@pytest.mark.parametrize("N,x", [(600, 250), (600, 586), (600, 13), (16, 2)])
+def test_rows_not_finite(device, causal, N, x):
+    """A row that is not finite reaches the rows whose working sets meet it
+    (586, 13 and 2: also the partners of positions outside the sequence, whose
+    windows hold its last and first rows)."""
+    k, pi, times = 4, 16, 49152 // (2 * N) + 1
     q, kk, v, gate, do = (many(t, times) for t in inputs(device, N, k, pi, False))
     idx = oracle.index_set(N, k, pi, causal=causal)
     meets = torch.from_numpy((idx == x).any(1)).to(device)   # queries whose set holds x
