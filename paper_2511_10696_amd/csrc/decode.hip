@@ -161,7 +161,8 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kernel(DecodeParams p) {
     if (w < nchunks) load(w);
     if (extra) {
         const float v = logit(kx, rg == 1 ? fb.partner : fb.local);
-        const float sc = rg == 0 || (rg == 1 && jp >= 0) ? v : -INFINITY;
+        const bool entry = rg == 0 || (rg == 1 && jp >= 0);
+        const float sc = entry ? v : -INFINITY;
         m = sc;
 #pragma unroll
         for (int o = LPR; o < 64; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
@@ -169,7 +170,7 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kernel(DecodeParams p) {
         l = pr;
         float vf[EPL];
         to_f32<T>(vx, vf);
-        if (sc != -INFINITY) {
+        if (entry) {
 #pragma unroll
             for (int e = 0; e < EPL; ++e) acc[e] = pr * vf[e];
         }

@@ -39,3 +39,22 @@ def test_decode_chunk_edges(device, dtype, D, S, H, chunks):
     assert np.abs(np32(lse) - lref).max() <= LSE_TOL
     for s, t in enumerate(lens_np):
         assert torch.equal(kc[s, :, t], kn[s]) and torch.equal(vc[s, :, t], vn[s])
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_partner_of_weight_zero(device, dtype):
+    """A partner whose logit is -inf has weight 0: of its value, an infinity
+    makes NaN (0 times inf) where it stands, as it does in a window row, and
+    nothing else shows."""
+    D, k, pi, t = 64, 40, 70, 90
+    g = torch.Generator(device="cuda").manual_seed(32)
+    kc, vc = (torch.randn(1, 2, 128, D, generator=g, device="cuda").to(dtype) for _ in range(2))
+    qn, kn, vn = (torch.randn(1, 2, D, generator=g, device="cuda").to(dtype) for _ in range(3))
+    qn[..., 0] = 1.0
+    kc[:, :, t - pi, 0], vc[:, :, t - pi, 5] = -float("inf"), float("inf")
+    lens = torch.tensor([t], dtype=torch.int32, device="cuda")
+    gate = torch.zeros(2, device="cuda")
+    out = pa.pi_attn_decode_step(lens, qn, kn, vn, kc.clone(), vc.clone(), gate, k, pi)
+    assert torch.isnan(out[..., 5]).all()
+    out[..., 5] = 0
+    assert torch.isfinite(out).all()
