@@ -173,7 +173,8 @@ __global__ __launch_bounds__(NT) void backward_kv_bf16_kernel(BwdParams bp, int 
     // one of these keys and (bidirectional) [par2_lo, par2_hi) whose
     // partner t + pi is, are handled after the band.
     const int band_lo = BIDIR ? window_lo(j0, kw) & ~31 : j0;
-    const int band_hi = BIDIR ? (int)min((int64_t)j0 + BK + kw, (int64_t)QE) : min(QE, j0 + BK + kw);
+    // (k may be any int: sums with it are 64-bit, or written as differences)
+    const int band_hi = (int)min((int64_t)j0 + BK + kw, (int64_t)QE);
     const int ntiles = band_hi > band_lo ? (band_hi - band_lo + TQ - 1) / TQ : 0;
     const bool has_par = partner_enabled(kw, pi) && (int64_t)j0 + pi < QE;
     const int par_lo = j0 + pi;
@@ -235,12 +236,12 @@ __global__ __launch_bounds__(NT) void backward_kv_bf16_kernel(BwdParams bp, int 
     // the block needs masking.
     auto active = [&](int t0b) {
         if constexpr (BIDIR) return t0b < band_hi && kq0 < NK && t0b - (kq0 + 31) <= kw && t0b + 31 >= kq0 - kw;
-        return t0b < band_hi && kq0 < NK && t0b <= kq0 + 31 + kw && t0b + 31 >= kq0;
+        return t0b < band_hi && kq0 < NK && t0b - (kq0 + 31) <= kw && t0b + 31 >= kq0;
     };
     auto edge_block = [&](int t0b) {
         return BIDIR ? !(t0b + 31 - kq0 <= kw && kq0 + 31 - t0b <= kw) || t0b + 31 >= QE || kq0 + 31 >= NK ||
                            t0b < QS
-                     : !(t0b >= kq0 + 31 && t0b + 31 <= kq0 + kw) || t0b + 31 >= QE || kq0 + 31 >= NK;
+                     : !(t0b >= kq0 + 31 && t0b + 31 - kq0 <= kw) || t0b + 31 >= QE || kq0 + 31 >= NK;
     };
 
     // First phase of a block (rows 32 blk.. of tile tb, first query t0b):
@@ -298,7 +299,7 @@ __global__ __launch_bounds__(NT) void backward_kv_bf16_kernel(BwdParams bp, int 
         if (edge) {
             asm volatile("" ::: "memory");
             const int lo = max(BIDIR ? j - kw : j, max(QS, t0b));
-            const int hi = min(j + kw, min(QE - 1, t0b + 31));
+            const int hi = (int)min((int64_t)j + kw, (int64_t)min(QE - 1, t0b + 31));
             const int n = hi - lo + 1;
             uint32_t keep = !j_ok || n <= 0 ? 0u : n >= 32 ? ~0u : ((1u << n) - 1u) << (lo - t0b);
             keep >>= 4 * g;
