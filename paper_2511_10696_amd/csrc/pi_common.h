@@ -136,7 +136,9 @@ __device__ inline Order tile_order(uint32_t logical, int n_tiles, int H) {
 // ---- direct global-to-LDS tile fetch ---------------------------------------
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kOutOfRange = 1 << 30;   // past any tile range the descriptors describe
+// At or past the end of every range that a descriptor describes: the argument
+// checks keep ranges below 2^31 bytes, and they are multiples of 16.
+constexpr int kOutOfRange = 0x7ffffff0;
 
 // Raw buffer descriptor over nbytes from base (stride 0; word 3 is the gfx9
 // raw-buffer format: 32-bit data, range checked).
