@@ -129,8 +129,9 @@ __global__ __launch_bounds__(NT, 2) void backward_q_bf16_kernel(BwdParams bp, in
     const int kend = min(BIDIR ? (int)min((int64_t)t0 + BM + kw, (int64_t)NS) : min(t0 + BM, NQ), p.kvend);
     const int ntiles = (kend - kb0 + TK - 1) / TK;
     const int rowb = (int)(2 * ksn);
-    const u32x4 rk = raw_rsrc(kp + (int64_t)kb0 * ksn, (kend - kb0) * rowb);
-    const u32x4 rv = raw_rsrc(vp + (int64_t)kb0 * ksn, (kend - kb0) * rowb);
+    // up to the last row's end (row strides may be below D, or 0)
+    const int band = (kend - kb0 - 1) * rowb + 2 * D;
+    const u32x4 rk = raw_rsrc(kp + (int64_t)kb0 * ksn, band), rv = raw_rsrc(vp + (int64_t)kb0 * ksn, band);
     if (ntiles > 0) tile_fetch<D>(tA, rk, rv, rowb, 0, w, lane);
 
     // Query and dL/dy rows as B operands (lanes without a query hold zeros).

@@ -296,10 +296,11 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void forward_bf16_kernel(FwdPa
     // ---- prologue: every load is issued before any is waited for ----------
     // (the query fragments, the gate logit, the partner key/value rows, then
     // the first tile), so the prologue costs one memory round trip.
-    // Buffer descriptors over rows [kb0, kend) of this head's keys and values.
+    // Buffer descriptors over rows [kb0, kend) of this head's keys and values,
+    // up to the last row's end (row strides may be below D, or 0).
     const int rowb = (int)(2 * ksn);
-    const u32x4 rk = raw_rsrc(kp + (int64_t)kb0 * ksn, (kend - kb0) * rowb);
-    const u32x4 rv = raw_rsrc(vp + (int64_t)kb0 * ksn, (kend - kb0) * rowb);
+    const int band = (kend - kb0 - 1) * rowb + T::ROW_BYTES;
+    const u32x4 rk = raw_rsrc(kp + (int64_t)kb0 * ksn, band), rv = raw_rsrc(vp + (int64_t)kb0 * ksn, band);
 
     // Loads use a clamped, always-readable row; lanes without a query or a
     // partner zero the data afterwards.

@@ -121,17 +121,15 @@ __global__ __launch_bounds__(NT) void smallk_bf16_kernel(FwdParams p, GateMlp m,
         const int64_t base = b * p.sb + h * p.sh;
         const __bf16 *kp = (const __bf16 *)p.k_ptr + base;
         const __bf16 *vp = (const __bf16 *)p.v + base;
-        const __amdgpu_buffer_rsrc_t rk =
-            __builtin_amdgcn_make_buffer_rsrc((void *)(kp + (int64_t)lo * p.sn), (short)0, (hi - lo) * rowb_g, 0x00020000);
-        const __amdgpu_buffer_rsrc_t rv =
-            __builtin_amdgcn_make_buffer_rsrc((void *)(vp + (int64_t)lo * p.sn), (short)0, (hi - lo) * rowb_g, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rk = row_range<D>(kp + (int64_t)lo * p.sn, hi - lo, rowb_g);
+        const __amdgpu_buffer_rsrc_t rv = row_range<D>(vp + (int64_t)lo * p.sn, hi - lo, rowb_g);
 #pragma unroll
         for (int u = 0; u < BD::CH; ++u) {
             const int cid = tid + NT * u;
             const int r = cid / CPR, c = cid % CPR;
             const int gr = rlo + r;
-            // rows outside [lo, hi) read as zeros (offset past the range)
-            const int off = (gr >= lo && gr < hi && r < BD::ROWS) ? (gr - lo) * rowb_g + 16 * c : (hi - lo) * rowb_g;
+            // rows outside [lo, hi) read as zeros
+            const int off = (gr >= lo && gr < hi && r < BD::ROWS) ? (gr - lo) * rowb_g + 16 * c : kOutOfRange;
             nx.k[u] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rk, off, 0, 0));
             nx.v[u] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rv, off, 0, 0));
         }

@@ -92,16 +92,14 @@ __global__ __launch_bounds__(NT) void smallk_bwd_q_kernel(BwdParams bp, Grid gd)
         const int64_t base = b * p.sb + h * p.sh;
         const __bf16 *kp = (const __bf16 *)p.k_ptr + base;
         const __bf16 *vp = (const __bf16 *)p.v + base;
-        const __amdgpu_buffer_rsrc_t rk =
-            __builtin_amdgcn_make_buffer_rsrc((void *)(kp + (int64_t)lo * p.sn), (short)0, (hi - lo) * rowb_g, 0x00020000);
-        const __amdgpu_buffer_rsrc_t rv =
-            __builtin_amdgcn_make_buffer_rsrc((void *)(vp + (int64_t)lo * p.sn), (short)0, (hi - lo) * rowb_g, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rk = row_range<D>(kp + (int64_t)lo * p.sn, hi - lo, rowb_g);
+        const __amdgpu_buffer_rsrc_t rv = row_range<D>(vp + (int64_t)lo * p.sn, hi - lo, rowb_g);
 #pragma unroll
         for (int u = 0; u < BD::CH; ++u) {
             const int cid = tid + NT * u;
             const int r = cid / CPR, c = cid % CPR;
             const int gr = rlo + r;
-            const int off = (gr >= lo && gr < hi && r < BD::ROWS) ? (gr - lo) * rowb_g + 16 * c : (hi - lo) * rowb_g;
+            const int off = (gr >= lo && gr < hi && r < BD::ROWS) ? (gr - lo) * rowb_g + 16 * c : kOutOfRange;
             nx.k[u] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rk, off, 0, 0));
             nx.v[u] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rv, off, 0, 0));
         }
@@ -271,18 +269,16 @@ __global__ __launch_bounds__(NT) void smallk_bwd_kv_kernel(BwdParams bp, Grid gd
         const int64_t rbase = ((int64_t)b * p.H + h) * N;
         const __bf16 *qp = (const __bf16 *)p.q + base;
         const __bf16 *op = (const __bf16 *)bp.dout + obase;
-        const __amdgpu_buffer_rsrc_t rq =
-            __builtin_amdgcn_make_buffer_rsrc((void *)(qp + (int64_t)lo * p.sn), (short)0, (hi - lo) * rowq_g, 0x00020000);
-        const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)(op + (int64_t)lo * bp.osn), (short)0, (hi - lo) * rowo_g, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rq = row_range<D>(qp + (int64_t)lo * p.sn, hi - lo, rowq_g);
+        const __amdgpu_buffer_rsrc_t ro = row_range<D>(op + (int64_t)lo * bp.osn, hi - lo, rowo_g);
 #pragma unroll
         for (int u = 0; u < BD::CH; ++u) {
             const int cid = tid + NT * u;
             const int r = cid / CPR, c = cid % CPR;
             const int gr = qlo + r;
             const bool in = gr >= lo && gr < hi && r < BD::ROWS;
-            const int offq = in ? (gr - lo) * rowq_g + 16 * c : (hi - lo) * rowq_g;
-            const int offo = in ? (gr - lo) * rowo_g + 16 * c : (hi - lo) * rowo_g;
+            const int offq = in ? (gr - lo) * rowq_g + 16 * c : kOutOfRange;
+            const int offo = in ? (gr - lo) * rowo_g + 16 * c : kOutOfRange;
             nx.q[u] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rq, offq, 0, 0));
             nx.o[u] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(ro, offo, 0, 0));
         }

@@ -30,6 +30,13 @@ struct Band {
     static constexpr int E = D / 8;                               // dimensions per lane
 };
 
+// Buffer descriptor of n rows of D elements, rowb bytes apart (0 and less than
+// a row's own bytes included): up to the last row's end.
+template <int D>
+__device__ inline __amdgpu_buffer_rsrc_t row_range(const __bf16 *first, int n, int rowb) {
+    return __builtin_amdgcn_make_buffer_rsrc((void *)first, (short)0, (n - 1) * rowb + 2 * D, 0x00020000);
+}
+
 // LDS position of 16-byte chunk c of band row r.  D = 128: the two halves of
 // a row swap on odd rows, so the 8 lanes of neighbouring queries (adjacent
 // rows) read disjoint banks.
