@@ -1,10 +1,11 @@
 // decode.hip -- one KV-cached decode step of causal pi-Attention, bf16 or
 // float32 caches, fp32 arithmetic, D = 64 or 128.
 //
-// One work-group per (sequence s, head h); t = len_in[s].  The working set
-// W_t (Sec. 3.5, eq. online_ws) is the cache window rows max(0,t-k)..t-1,
-// the partner row t-pi (when pi > k and t >= pi) and the new row t itself,
-// which is taken from k_new/v_new and also appended to the caches.
+// One work-group of one to eight wavefronts per (sequence s, head h); t =
+// len_in[s].  The working set W_t (Sec. 3.5, eq. online_ws) is the cache
+// window rows max(0,t-k)..t-1, the partner row t-pi (when pi > k and t >= pi)
+// and the new row t itself, which is taken from k_new/v_new and also appended
+// to the caches.
 //
 // The window rows are split across the work-group's wavefronts in chunks of
 // CH load instructions: a row is covered by LPR lanes with 16-byte loads, so
@@ -18,10 +19,13 @@
 // wavefronts are merged in LDS at the end (max, rescaled sums).
 //
 // What bounds it: HBM reads at large launches, one round trip (lengths, then
-// rows) plus the merge at small ones.  Before and after the wavefront rule,
-// the extra slot and the loads below: 12.8 -> 7.6 us at one sequence of 32
-// heads (D = 128, k = 512), 96.2 -> 82.4 us at 64; float32 caches (which had
-// one wavefront per (s, h)) 379 -> 159 us at 64 x 32.
+// rows) plus the merge at small ones, the wavefronts' own instructions at
+// windows of a few rows (a chunk's slots are worked on whether they hold a row
+// or not, so short windows take short chunks).  The wavefront rule, the extra
+// slot and the loads below together, against four wavefronts of eight slots
+// (bf16) and one wavefront, row after row (float32): bf16 12.4 -> 6.5 us at one
+// sequence of 32 heads (D = 128, k = 512), 98.9 -> 81.8 us at 64; float32
+// 379 -> 167 us at 64.
 #include <algorithm>
 
 #include "kernels.h"
@@ -34,24 +38,18 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int CH = 8;   // load instructions per chunk
-
 template <typename T, int D>
 struct Row {
     static constexpr int EPL = 16 / (int)sizeof(T);   // elements per lane
     static constexpr int LPR = D / EPL;               // lanes per row
     static constexpr int RPI = 64 / LPR;              // rows per load instruction
-    static constexpr int RPC = RPI * CH;              // rows per chunk
 };
 
 typedef unsigned raw16 __attribute__((ext_vector_type(4)));
 
 __device__ inline uint4 ld16(const void *p) { return *reinterpret_cast<const uint4 *>(p); }
 
-// A window row's load: each row is read once per step, so it is not kept in
-// the caches (92.7 -> 82.4 us a step at 64 x 32 (s, h), D = 128, k = 512, 541
-// MB: 5.8 -> 6.6 TB/s; 21.6 -> 22.2 us at 16 x 32, where the rows of one step
-// are still in the last-level cache at the next).
+// A window row's load that does not keep the row in the caches.
 __device__ inline uint4 ld16_once(const void *p) {
     return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const raw16 *>(p)));
 }
@@ -82,10 +80,12 @@ __device__ inline float row_sum(float x) {
     return x;
 }
 
-template <typename T, int D, bool CLAMP, int WAVES>
+// CH: load instructions per chunk; ONCE: window rows are not kept in the caches.
+template <typename T, int D, bool CLAMP, int WAVES, int CH, bool ONCE>
 __global__ __launch_bounds__(64 * WAVES) void decode_kernel(DecodeParams p) {
     using R = Row<T, D>;
-    constexpr int LPR = R::LPR, RPI = R::RPI, RPC = R::RPC, EPL = R::EPL;
+    constexpr int LPR = R::LPR, RPI = R::RPI, EPL = R::EPL;
+    constexpr int RPC = RPI * CH;   // rows per chunk
 
     __shared__ float s_m[WAVES], s_l[WAVES];
     __shared__ float s_acc[WAVES][D];
@@ -100,7 +100,7 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kernel(DecodeParams p) {
     T *out = (T *)p.out + sh * D;
 
     if (t < 0 || t >= p.cap) {
-        if (tid < D) out[tid] = (T)NAN;
+        for (int d = tid; d < D; d += 64 * WAVES) out[d] = (T)NAN;
         if (tid == 0) {
             if (p.lse) p.lse[sh] = NAN;
             if (p.len_out && h == 0) p.len_out[s] = t;
@@ -123,14 +123,14 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kernel(DecodeParams p) {
     const int jp = partner_of(t, p.k, p.pi);
 
     uint4 kr[CH], vr[CH];
+    // Slots past the window read its last row again (and count as zeros below):
+    // behind a branch each, every load was waited for before the next.
     auto load = [&](int ch) __attribute__((always_inline)) {
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-            const int i = ch * RPC + c * RPI + rg;
-            const bool in = i < nwin;
-            const int64_t off = (int64_t)(lo + i) * D;
-            kr[c] = in ? ld16_once(kc + off) : make_uint4(0, 0, 0, 0);
-            vr[c] = in ? ld16_once(vc + off) : make_uint4(0, 0, 0, 0);
+            const int64_t off = (int64_t)(lo + min(ch * RPC + c * RPI + rg, nwin - 1)) * D;
+            kr[c] = ONCE ? ld16_once(kc + off) : ld16(kc + off);
+            vr[c] = ONCE ? ld16_once(vc + off) : ld16(vc + off);
         }
     };
     // logit (log2 units) of a row from this lane's part of it
@@ -199,6 +199,11 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kernel(DecodeParams p) {
         l *= alpha;
 #pragma unroll
         for (int e = 0; e < EPL; ++e) acc[e] *= alpha;
+        if ((ch + 1) * RPC > nwin) {
+#pragma unroll
+            for (int c = 0; c < CH; ++c)
+                if (ch * RPC + c * RPI + rg >= nwin) vr[c] = make_uint4(0, 0, 0, 0);
+        }
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
             const float pr = __builtin_amdgcn_exp2f(sc[c] - m_use);
@@ -227,7 +232,7 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kernel(DecodeParams p) {
     }
     __syncthreads();
 
-    if (tid < D) {
+    for (int d = tid; d < D; d += 64 * WAVES) {
         float M = -INFINITY;
 #pragma unroll
         for (int i = 0; i < WAVES; ++i) M = fmaxf(M, s_m[i]);
@@ -236,30 +241,52 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kernel(DecodeParams p) {
         for (int i = 0; i < WAVES; ++i) {
             const float f = s_m[i] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(s_m[i] - M);
             L += s_l[i] * f;
-            o += s_acc[i][tid] * f;
+            o += s_acc[i][d] * f;
         }
-        out[tid] = (T)(o / L);
-        if (tid == 0) {
+        out[d] = (T)(o / L);
+        if (d == 0) {
             if (p.lse) p.lse[sh] = (M + __log2f(L)) * kLn2 + fb.lse_shift;
             if (p.len_out && h == 0) p.len_out[s] = t + 1;
         }
     }
 }
 
-// Wavefronts per work-group.  Eight read a window of more than eight chunks
-// faster at every launch size (bf16, D = 128, k = 512: 7.9 against 9.1 us at
-// 32 (s, h), 22.0 against 22.3 us at 512, 92.6 against 96.0 us at 2048), and
-// a shorter one only while they do not crowd the chip (D = 64: 5.3 against
-// 5.6 us at 24 (s, h) and k = 389, 13.8 against 13.2 us at 512 and k = 465);
-// with four chunks or fewer they idle (25.3 against 22.0 us at 2048 and k =
-// 256).  Sixteen: 8.0 us at 32, 112 us at 2048.
+// ONCE, by the bytes of a step's window rows: they are read once, and kept in
+// the caches they only push out what is there.  With the caches of several
+// layers in turn (more than the last-level cache together), bf16, D = 128, k =
+// 512: 26.6 -> 23.5 us at 16 x 32 (s, h) (134 MB a step), 47.8 -> 42.6 us at
+// 32 x 32, 91.0 -> 82.6 us at 64 x 32 (5.9 -> 6.5 TB/s).  The rows of a small
+// step lie in the L2s at the next one, if nothing else ran, and cost no more
+// when kept even if they do not: 5.3 us kept and 5.8 us not at 32 (s, h) (D =
+// 64, k = 384, 3 MB), and from 17 MB on the other way round.
+constexpr int64_t kKeepBytes = 12 << 20;
+
+template <typename T, int D, bool CLAMP, int WAVES, int CH>
+hipError_t launch_n(const DecodeParams &p, hipStream_t stream) {
+    const int64_t n = (int64_t)p.S * p.H;
+    const bool once = 2 * n * std::min(p.k, p.cap) * D * (int64_t)sizeof(T) > kKeepBytes;
+    return launch_kernel(once ? decode_kernel<T, D, CLAMP, WAVES, CH, true> : decode_kernel<T, D, CLAMP, WAVES, CH, false>,
+                         dim3((unsigned)n), dim3(64 * WAVES), stream, p);
+}
+
+// Wavefronts and chunk size, by the window's load instructions (of keys) and
+// the launch; each within 8% of the best of one to eight wavefronts of two,
+// four and eight slots, caches in turn and the same ones again, from 32 to
+// 32768 (s, h), both dtypes, D = 64 and 128.  Against four wavefronts of eight
+// slots: a chip full of short windows is bound by its wavefronts (loads <= 2:
+// 2.1 to 3 times as fast from 4096 (s, h) on, float32 D = 64, k = 4 at 8192:
+// 22 -> 9.4 us; 3 to 8: 1.2 to 1.8 times), a few (s, h) by one wavefront's
+// chain (9 to 32 loads at 32 and 256 (s, h): equal to 12% faster), and eight
+// wavefronts of eight slots stream long windows best from 33 loads on (1 to 3%
+// at 4096 (s, h), 12% at 32 and 128 loads; below, up to 1.7 times as long).
 template <typename T, int D, bool CLAMP>
 hipError_t launch_w(const DecodeParams &p, hipStream_t stream) {
     const int64_t n = (int64_t)p.S * p.H;
-    const int chunks = (std::min(p.k, p.cap) + Row<T, D>::RPC - 1) / Row<T, D>::RPC;
-    if (chunks > 8 || (chunks > 4 && n <= 256))
-        return launch_kernel(decode_kernel<T, D, CLAMP, 8>, dim3((unsigned)n), dim3(512), stream, p);
-    return launch_kernel(decode_kernel<T, D, CLAMP, 4>, dim3((unsigned)n), dim3(256), stream, p);
+    const int loads = (std::min(p.k, p.cap) + Row<T, D>::RPI - 1) / Row<T, D>::RPI;
+    if (loads > 32) return launch_n<T, D, CLAMP, 8, 8>(p, stream);
+    if (loads > 8 || (loads > 4 && n <= 1024)) return launch_n<T, D, CLAMP, 4, 4>(p, stream);
+    if (loads > 2 || n < 2048) return launch_n<T, D, CLAMP, 2, 2>(p, stream);
+    return launch_n<T, D, CLAMP, 1, 2>(p, stream);
 }
 
 template <typename T>

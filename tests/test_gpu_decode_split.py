@@ -1,8 +1,7 @@
 """The decode step at the edges of its wavefront split: windows of one row more
-and less than whole chunks (a chunk is 8 load instructions of 1 KiB), partner
-present, absent and next to the window, with four and eight wavefronts per
-work-group, both sides of each line of that choice.  Bars as in
-test_gpu_parity.py."""
+and less than whole chunks (up to 8 load instructions of 1 KiB), partner
+present, absent and next to the window, with one to eight wavefronts per (s, h),
+both sides of each line of that choice.  Bars as in test_gpu_parity.py."""
 import numpy as np
 import pytest
 import torch
@@ -39,6 +38,54 @@ def test_decode_chunk_edges(device, dtype, D, S, H, chunks):
     assert np.abs(np32(lse) - lref).max() <= LSE_TOL
     for s, t in enumerate(lens_np):
         assert torch.equal(kc[s, :, t], kn[s]) and torch.equal(vc[s, :, t], vn[s])
+
+
+@pytest.mark.parametrize("dtype,D", [(torch.bfloat16, 64), (torch.bfloat16, 128), (torch.float32, 64),
+                                     (torch.float32, 128)])
+@pytest.mark.parametrize("S,H", [(8, 4), (8, 129), (8, 256)])   # 32, 1032 and 2048 (s, h)
+@pytest.mark.parametrize("loads", [0, 1, 2, 3, 5, 9])
+def test_decode_short_windows(device, dtype, D, S, H, loads):
+    """Windows of a few load instructions; the heads of a few (oracle) many
+    times over give the same rows in every copy."""
+    few = 4
+    rpi = 1024 // (D * (2 if dtype == torch.bfloat16 else 4))   # rows per load instruction
+    k = max(0, loads * rpi - (loads > 3))
+    pi, cap = k + 1, k + 30
+    lens_np = np.array([0, 1, max(k - 1, 2), k + 1, k + 2, k + 3, cap - 2, cap - 1], np.int32)
+    g = torch.Generator(device="cuda").manual_seed(33)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda").to(dtype)
+    kc, vc, qn, kn, vn = rnd(S, few, cap, D), rnd(S, few, cap, D), rnd(S, few, D), rnd(S, few, D), rnd(S, few, D)
+    gate = torch.rand(few, generator=g, device="cuda") * 2 - 1
+    for s, t in enumerate(lens_np):   # rows past the length are never read
+        kc[s, :, t:], vc[s, :, t:] = float("nan"), float("nan")
+    ref, lref = oracle.decode_step(lens_np, qn, kn, vn, np32(kc), np32(vc), gate, k, pi, want_lse=True)
+    times = (H + few - 1) // few
+    rep = lambda x: x.repeat_interleave(times, 1)[:, :H].contiguous()
+    kcb, vcb, lse = rep(kc), rep(vc), torch.empty(S, H, device="cuda")
+    lens, lout = torch.tensor(lens_np, device="cuda"), torch.empty(S, dtype=torch.int32, device="cuda")
+    out = pa.pi_attn_decode_step(lens, rep(qn), rep(kn), rep(vn), kcb, vcb, gate.repeat_interleave(times)[:H], k, pi,
+                                 lse=lse, len_out=lout)
+    assert torch.equal(lout, lens + 1)
+    for i in range(0, H, times):
+        assert torch.equal(out[:, i:i + times], out[:, i:i + 1].expand(-1, min(times, H - i), -1))
+        assert_close(np32(out[:, i]), ref[:, i // times], dtype)
+        assert np.abs(np32(lse[:, i]) - lref[:, i // times]).max() <= LSE_TOL
+    for s, t in enumerate(lens_np):
+        assert torch.equal(kcb[s, :, t], rep(kn)[s]) and torch.equal(vcb[s, :, t], rep(vn)[s])
+
+
+def test_rows_kept_or_not(device):
+    """Steps of more and of less than 12 MB of window rows (kept in the caches
+    or not): the same sequence in either gives the same output."""
+    H, D, k, pi, t = 8, 128, 300, 400, 450
+    g = torch.Generator(device="cuda").manual_seed(34)
+    kc, vc = (torch.randn((1, H, 460, D), generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+    qn, kn, vn = (torch.randn((1, H, D), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    gate = torch.zeros(H, device="cuda")
+    step = lambda S: pa.pi_attn_decode_step(torch.full((S,), t, dtype=torch.int32, device="cuda"), *(
+        x.repeat(S, *([1] * (x.dim() - 1))) for x in (qn, kn, vn, kc, vc)), gate, k, pi)
+    few, many = step(2), step(30)   # 2.5 and 37 MB
+    assert torch.equal(few[:1].expand(30, -1, -1), many)
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
