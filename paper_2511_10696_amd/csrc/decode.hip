@@ -279,10 +279,12 @@ hipError_t launch_n(const DecodeParams &p, hipStream_t stream) {
 // chain (9 to 32 loads at 32 and 256 (s, h): equal to 12% faster), and eight
 // wavefronts of eight slots stream long windows best from 33 loads on (1 to 3%
 // at 4096 (s, h), 12% at 32 and 128 loads; below, up to 1.7 times as long).
+// A launch has fewer than 2^32 threads: from 2^24 (s, h) on, one wavefront.
 template <typename T, int D, bool CLAMP>
 hipError_t launch_w(const DecodeParams &p, hipStream_t stream) {
     const int64_t n = (int64_t)p.S * p.H;
     const int loads = (std::min(p.k, p.cap) + Row<T, D>::RPI - 1) / Row<T, D>::RPI;
+    if (n >= (1 << 24)) return launch_n<T, D, CLAMP, 1, 2>(p, stream);
     if (loads > 32) return launch_n<T, D, CLAMP, 8, 8>(p, stream);
     if (loads > 8 || (loads > 4 && n <= 1024)) return launch_n<T, D, CLAMP, 4, 4>(p, stream);
     if (loads > 2 || n < 2048) return launch_n<T, D, CLAMP, 2, 2>(p, stream);

@@ -88,6 +88,16 @@ def test_rows_kept_or_not(device):
     assert torch.equal(few[:1].expand(30, -1, -1), many)
 
 
+def test_more_heads_than_a_launch_of_wide_groups(device):
+    """2^24 (s, h) of float32 caches of one row: the new row alone."""
+    S, H, D = 1 << 20, 16, 64
+    kc, vc = (torch.zeros((S, H, 1, D), device="cuda") for _ in range(2))
+    x = torch.randn((S, H, D), generator=torch.Generator("cuda").manual_seed(35), device="cuda")
+    lens, gate = torch.zeros(S, dtype=torch.int32, device="cuda"), torch.zeros(H, device="cuda")
+    out = pa.pi_attn_decode_step(lens, x, x, x, kc, vc, gate, 0, 0)
+    assert torch.equal(out, x) and torch.equal(kc[:, :, 0], x) and torch.equal(vc[:, :, 0], x)
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_partner_of_weight_zero(device, dtype):
     """A partner whose logit is -inf has weight 0: of its value, an infinity
