@@ -30,12 +30,13 @@ hipError_t launch_forward_smallk(const FwdParams &p, const GateMlp *mlp, hipStre
 // The gate logits alone, into mlp.gate_out (bf16 on MFMA, float32 on VALU).
 hipError_t launch_gate_logits(const FwdParams &p, const GateMlp &mlp, int dtype, hipStream_t stream);
 
-// Small-window backward (k <= kSmallK), bf16, D = 64 or 128: a query pass
-// (dq, gate gradient, exact row terms) and a key pass (dk, dv), both in the
-// forward's work decomposition.  Needs the forward's lse.
+// Small-window backward (k <= kSmallK), bf16, D = 64 or 128: dq, dk, dv, gate
+// gradient and exact row terms, in one pass over the sequence where that takes
+// the call, otherwise in a query pass and a key pass in the forward's work
+// decomposition.  Needs the forward's lse.
 hipError_t launch_backward_smallk(const BwdParams &p, hipStream_t stream);
 
-// The same in one pass over the sequence, and whether it takes the call.
+// The one pass, and whether it takes the call.
 bool smallk_fused_takes(const BwdParams &p);
 hipError_t launch_backward_smallk_fused(const BwdParams &p, hipStream_t stream);
 

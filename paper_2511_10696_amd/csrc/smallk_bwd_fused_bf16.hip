@@ -299,12 +299,14 @@ hipError_t launch_k(const BwdParams &p, hipStream_t stream) {
 // step fit beside the ring (at k = 12 the two take 292 us at B8 H16 N4096, as
 // one does) and launches that fill the chip (one run takes its steps one after
 // the other: 22.7 against 20.4 us in two passes at 32000 rows, 31 against 38
-// us at 64000).
+// us at 64000).  It takes a work-group for every (b, h) where the two passes
+// take one for up to 32 heads, and a launch has fewer than 2^32 threads.
 bool smallk_fused_takes(const BwdParams &p) {
     const FwdParams &f = p.f;
     const int reach = partner_enabled(f.k, f.pi) ? f.pi : f.k;
-    return f.D == 64 && f.k <= 8 && reach <= (f.causal ? Ring<false>::REACH : Ring<true>::REACH) &&
-           (int64_t)f.B * f.H * f.N >= 49152;
+    if (f.D != 64 || f.k > 8 || reach > (f.causal ? Ring<false>::REACH : Ring<true>::REACH)) return false;
+    const int64_t bh = (int64_t)f.B * f.H;
+    return bh * f.N >= 49152 && xcd_grid(bh) * NT < ((int64_t)1 << 32);
 }
 
 hipError_t launch_backward_smallk_fused(const BwdParams &p, hipStream_t stream) {

@@ -90,3 +90,20 @@ def test_rows_not_finite(device, causal, N, x):
         got = pa.pi_attn_backward(*args[:3], gate, k, pi, out, lse, args[3], **opt)
         for name, a, b, r in zip(("dq", "dk", "dv", "dgate"), clean, got, rows):
             assert torch.equal(a[:, :, ~r], b[:, :, ~r]), name
+
+
+def test_more_heads_than_a_launch_of_one_each(device):
+    """2^24 (b, h) of two rows: the two passes, which group heads, take the
+    call (its inputs one batch entry, expanded)."""
+    B, H, N, D = 1 << 20, 16, 2, 64
+    q, kk, v, do = (torch.randn((1, H, N, D), generator=torch.Generator("cuda").manual_seed(55 + i), device="cuda")
+                    .to(torch.bfloat16) for i in range(4))
+    gate = torch.rand(H, device="cuda")
+    out, lse = pa.pi_attn_forward(q, kk, v, gate, 2, 0, return_lse=True)
+    few = pa.pi_attn_backward(q, kk, v, gate, 2, 0, out, lse, do, gate_grad_per_query=True)
+    wide = lambda x: x.expand(B, *x.shape[1:])
+    got = pa.pi_attn_backward(*map(wide, (q, kk, v)), gate, 2, 0, wide(out), wide(lse).contiguous(), wide(do),
+                              gate_grad_per_query=True)
+    for name, a, b in zip(("dq", "dk", "dv", "dgate"), few, got):
+        for part in b.split(1 << 17):
+            assert torch.equal(part, a.expand(part.shape)), name
