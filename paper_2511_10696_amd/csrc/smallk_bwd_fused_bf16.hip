@@ -299,14 +299,23 @@ hipError_t launch_k(const BwdParams &p, hipStream_t stream) {
 // step fit beside the ring (at k = 12 the two take 292 us at B8 H16 N4096, as
 // one does) and launches that fill the chip (one run takes its steps one after
 // the other: 22.7 against 20.4 us in two passes at 32000 rows, 31 against 38
-// us at 64000).  It takes a work-group for every (b, h) where the two passes
-// take one for up to 32 heads, and a launch has fewer than 2^32 threads.
+// us at 64000).  A sequence of a tile or two takes more steps (N + reach rows,
+// bidirectionally N + 2 reach) than the two passes have tiles, and a step costs
+// the more the longer the window: at twice as many, k = 8, causal 1.09 times
+// the two passes' time (N = 31, pi = 16), bidirectional k = 4 1.17 to 1.4 times
+// (N = 4 to 32; N = 33 and 40, 3 steps for 2 tiles, equal), at 1.5 times as
+// many, bidirectional k = 8 1.06 to 1.09 times (N = 50, 64; pi = 9).
+// It takes a work-group for every (b, h) where the two passes take one for up
+// to 32 heads, and a launch has fewer than 2^32 threads.
 bool smallk_fused_takes(const BwdParams &p) {
     const FwdParams &f = p.f;
     const int reach = partner_enabled(f.k, f.pi) ? f.pi : f.k;
     if (f.D != 64 || f.k > 8 || reach > (f.causal ? Ring<false>::REACH : Ring<true>::REACH)) return false;
     const int64_t bh = (int64_t)f.B * f.H;
-    return bh * f.N >= 49152 && xcd_grid(bh) * NT < ((int64_t)1 << 32);
+    if (bh * f.N < 49152 || xcd_grid(bh) * NT >= ((int64_t)1 << 32)) return false;
+    const int64_t steps = (f.N + (f.causal ? 1 : 2) * (int64_t)reach + STEP - 1) / STEP, tiles = (f.N + TT - 1) / TT;
+    if (f.causal) return f.k <= 4 || steps < 2 * tiles;
+    return f.k <= 4 ? steps < 2 * tiles : 2 * steps < 3 * tiles;
 }
 
 hipError_t launch_backward_smallk_fused(const BwdParams &p, hipStream_t stream) {

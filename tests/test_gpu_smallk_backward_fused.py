@@ -1,6 +1,6 @@
 """The one-pass small-window backward (D = 64, k <= 8, launches of at least
-49152 rows) against the two passes that smaller launches take: the same heads,
-a few times and many times over.  Both sum the same float32 terms, at most 19
+49152 rows, sequences of more than a tile or two) against the two passes that
+other launches take: the same heads, a few times and many times over.  Both sum the same float32 terms, at most 19
 a row and 64 dimensions a score, in another order: they agree to 2e-6 of the
 largest gradient, and the one pass meets the oracle at the bar of the two.
 Runs with ragged ends and of one and several steps, reaches of 0, k and pi up
@@ -19,7 +19,10 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = [(517, 4, 16, True), (1000, 4, 16, False), (300, 0, 0, True), (300, 0, 0, False), (129, 8, 32, True),
           (2049, 3, 9, False), (641, 8, 16, False), (96, 8, 5, True), (33, 4, 31, True), (40, 5, 6, False),
-          (700, 1, 16, False), (5, 4, 16, True)]
+          (700, 1, 16, False), (5, 4, 16, True),
+          # sequences of a tile or two, on both sides of the lines between one pass and two
+          (31, 8, 16, True), (33, 8, 16, True), (24, 4, 4, False), (25, 4, 4, False), (33, 4, 16, False),
+          (32, 8, 9, False), (64, 8, 9, False), (65, 8, 16, False)]
 
 
 def inputs(device, N, k, pi, pq, seed=51):
