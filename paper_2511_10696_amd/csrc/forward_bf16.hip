@@ -59,6 +59,8 @@
 // probability.  The lse, when requested, is taken from a second, fp32 sum of
 // the unrounded values (a separate instantiation keeps it off the common
 // path).
+#include <algorithm>
+
 #include "kernels.h"
 #include "pi_common.h"
 
@@ -250,23 +252,14 @@ __device__ inline void softmax_block(Wave<D> &ws, f32x16 &s, bool edge, int j0, 
     ws.lb = sum_bf16x8(pb[1], sum_bf16x8(pb[0], ws.lb));
 }
 
-template <int D, bool CLAMP, bool BIDIR, bool LSE, bool FULL>
+template <int D, bool CLAMP, bool BIDIR, bool LSE, bool FULL, bool HEADS>
 __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void forward_bf16_kernel(FwdParams p, int n_qt, uint32_t n_logical) {
     using T = Tile<D>;
     using W = Wave<D>;
     __shared__ TileBuf<D> tA, tB;
     const uint32_t logical = xcd_remap(blockIdx.x, n_logical);
     if (logical >= n_logical) return;
-    // Order: the tiles of a head one after the other (they share most of their
-    // keys), or, at D = 64 in launches that fill the chip (FULL), the heads of
-    // a tile: 36.2 -> 34.4 us at B4 H16 N4096 k128, 39.5 -> 34.7 us
-    // bidirectionally at B8 H12 N2000 ([B][N][H][D] storage), equal at k = 512;
-    // D = 128 loses (B1 H32 N32768 k512 487 -> 547 us: its band is read from
-    // HBM again), and so do small launches (8.1 -> 8.3 us at B1 H16 N1000, the
-    // same for the choice made at run time).  With the lse a backward follows,
-    // which starts on the tiles of a head: a training pass at the first shape
-    // takes 166.6 us in that order and 167.6 us in the other.
-    const Order o = tile_order<FULL && D == 64 && !LSE>(logical, n_qt, p.H);
+    const Order o = tile_order<HEADS>(logical, n_qt, p.H);
     const int qt = o.tile, h = o.h, b = o.b;
     const int64_t bh = o.bh;
 
@@ -589,6 +582,27 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void forward_bf16_kernel(FwdPa
     }
 }
 
+// Order of the work-groups: the tiles of a head one after the other (they
+// share most of their keys), or, at D = 64 in launches that fill the chip, the
+// heads of a tile: 36.2 -> 34.4 us at B4 H16 N4096 k128, 39.5 -> 34.7 us
+// bidirectionally at B8 H12 N2000 ([B][N][H][D] storage).  The 128 work-groups
+// resident on an XCD then hold the band of every head, H times the window's
+// rows (256 bytes of K and V each) more than those of one head, beside the 4
+// MB of their own rows; past 1 MB more they are read from memory again:
+// B2 H16 N8192 k256 (4096 rows) 41.2 us tiles first and 41.3 us heads first,
+// k512 58.8 and 60.6; B1 H64 N4096 k64 29.4 and 30.3, k128 33.2 and 37.9, k512
+// 58.8 and 75.8; bidirectionally B2 H32 N4096 k64 39.1 and 41.2, k512 99.6 and
+// 109.3.  At D = 128 a band is twice the bytes (B1 H32 N32768 k512 487 -> 547
+// us), and small launches lose (8.1 -> 8.3 us at B1 H16 N1000).  With the lse a
+// backward follows, which starts on the tiles of a head: a training pass at
+// the first shape takes 166.6 us in that order and 167.6 us in the other.
+constexpr int64_t kHeadsFirstRows = 4096;
+
+template <int D, bool LSE>
+constexpr bool heads_first() {
+    return D == 64 && !LSE;
+}
+
 template <int D, bool CLAMP, bool BIDIR, bool LSE>
 hipError_t launch(const FwdParams &p, hipStream_t stream) {
     const int n_qt = (p.N + BM - 1) / BM;
@@ -596,9 +610,12 @@ hipError_t launch(const FwdParams &p, hipStream_t stream) {
     if (n_logical == 0) return hipSuccess;
     const int64_t grid = xcd_grid(n_logical);
     const bool full = n_logical >= 1024;   // four work-groups per CU at D = 64
-    return launch_kernel(full ? forward_bf16_kernel<D, CLAMP, BIDIR, LSE, true>
-                              : forward_bf16_kernel<D, CLAMP, BIDIR, LSE, false>,
-                         dim3((unsigned)grid), dim3(NT), stream, p, n_qt, (uint32_t)n_logical);
+    auto kernel = full ? forward_bf16_kernel<D, CLAMP, BIDIR, LSE, true, false>
+                       : forward_bf16_kernel<D, CLAMP, BIDIR, LSE, false, false>;
+    if constexpr (heads_first<D, LSE>())
+        if (full && p.H * (int64_t)std::min(p.k, p.nseq) * (BIDIR ? 2 : 1) <= kHeadsFirstRows)
+            kernel = forward_bf16_kernel<D, CLAMP, BIDIR, LSE, true, true>;
+    return launch_kernel(kernel, dim3((unsigned)grid), dim3(NT), stream, p, n_qt, (uint32_t)n_logical);
 }
 
 template <int D, bool BIDIR, bool LSE>

@@ -34,6 +34,20 @@ def test_rows_stored_alike(device, D, N, k, pi, causal, strided):
             assert not with_lse or torch.equal(got[1][:, H * i:H * (i + 1)], lse)
 
 
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("H,k", [(64, 32), (64, 64), (64, 65), (128, 16), (1030, 3000)])
+def test_heads_first_alike(device, causal, H, k):
+    """Both sides of the line between the work-group orders at D = 64 (heads
+    times the window's rows): the order changes no bit."""
+    N, few = 1100, 2
+    cfg = W.ForwardConfig("custom", 1, few, N, 64, max(k, 17), 90, torch.bfloat16)
+    q, kk, v, gate = W.forward_inputs(cfg, 63, device, per_query_gate=True)
+    ref = pa.pi_attn_forward(q, kk, v, gate, cfg.k, cfg.pi, causal=causal)
+    out = pa.pi_attn_forward(*(many(x, H // few).repeat(2, *[1] * (x.dim() - 1)) for x in (q, kk, v, gate)), cfg.k, cfg.pi,
+                             causal=causal)
+    assert torch.equal(out, ref.repeat(2, H // few, 1, 1))
+
+
 def test_shard_queries_and_gradients_of_stride_zero(device):
     """Query (and dL/dy) rows of a shard call that are one row, repeated."""
     H, N, D, k, pi = 130, 300, 64, 40, 100
