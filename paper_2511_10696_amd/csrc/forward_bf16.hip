@@ -288,7 +288,14 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void forward_bf16_kernel(FwdPa
     const int ntiles = (kend - kb0 + TK - 1) / TK;
     // ---- prologue: every load is issued before any is waited for ----------
     // (the query fragments, the gate logit, the partner key/value rows, then
-    // the first tile), so the prologue costs one memory round trip.
+    // the first tile), so the prologue costs one memory round trip.  Causal at
+    // D = 128 the tile goes before the partners: the compiler moves one of
+    // their registers as soon as it is loaded, and a tile fetched after them
+    // waited a round trip for that (68.2 -> 60.5 us at B256 H16 N64 k17, 29.0
+    // -> 28.1 us at B64 H16 N128 k32, equal at N32768); bidirectionally, with
+    // the second partner behind the first, it gains nothing (763 -> 773 us at
+    // B1 H32 N32768 k512).
+    constexpr bool TILE_FIRST = D == 128 && !BIDIR;
     // Buffer descriptors over rows [kb0, kend) of this head's keys and values,
     // up to the last row's end (row strides may be below D, or 0).
     const int rowb = (int)(2 * ksn);
@@ -324,6 +331,8 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void forward_bf16_kernel(FwdPa
     }
     const float gl = p.gate[b * p.gsb + h * p.gsh + (tq - p.qpos0) * p.gsn];
 
+    if (TILE_FIRST && ntiles > 0) tile_fetch<D>(tA, rk, rv, rowb, 0, w, lane);
+
     // Partner rows: A-operand row c of the wavefront is row q0 + c - pi, the
     // partner of query q0 + c; the accumulator seed is that row's value, of
     // which lane (c, g) holds dims 32db + 8i + 4g + [0, 4).  Both rows are
@@ -354,7 +363,7 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void forward_bf16_kernel(FwdPa
             vff[s] = *reinterpret_cast<const bf16x8 *>(vp + frc * ksn + 16 * s + 8 * g);
         }
     }
-    if (ntiles > 0) tile_fetch<D>(tA, rk, rv, rowb, 0, w, lane);
+    if (!TILE_FIRST && ntiles > 0) tile_fetch<D>(tA, rk, rv, rowb, 0, w, lane);
     if constexpr (QLDS) {
         __builtin_amdgcn_s_waitcnt(0xF70);   // vmcnt(0): this wavefront's own fetches, read by itself alone
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
