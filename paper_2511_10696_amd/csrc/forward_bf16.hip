@@ -618,7 +618,11 @@ hipError_t launch(const FwdParams &p, hipStream_t stream) {
     const int64_t n_logical = (int64_t)p.B * p.H * n_qt;
     if (n_logical == 0) return hipSuccess;
     const int64_t grid = xcd_grid(n_logical);
-    const bool full = n_logical >= 1024;   // four work-groups per CU at D = 64
+    // FULL: four work-groups per CU at D = 64; at D = 128, with a tile of at
+    // most 40 queries (two wavefronts or one of the four), the barrier and the
+    // way through LDS cost more than whole lines save (2 to 6% of a launch at
+    // N = 20 and 32, 1 to 5% at 40, equal at 48, 5% gained at 64).
+    const bool full = n_logical >= 1024 && (D == 64 || p.N > 40);
     auto kernel = full ? forward_bf16_kernel<D, CLAMP, BIDIR, LSE, true, false>
                        : forward_bf16_kernel<D, CLAMP, BIDIR, LSE, false, false>;
     if constexpr (heads_first<D, LSE>())

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("N,k,pi", [(300, 40, 100), (129, 17, 18), (65, 100, 0), (1, 20, 30)])
+@pytest.mark.parametrize("N,k,pi", [(300, 40, 100), (129, 17, 18), (65, 100, 0), (1, 20, 30), (40, 17, 18), (41, 17, 18)])
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("strided", [True, False])
 def test_rows_stored_alike(device, D, N, k, pi, causal, strided):
