@@ -91,7 +91,7 @@ __device__ inline void read_vrows(bf16x8 f[Tile<D>::KS], const unsigned char *ti
     for (int s = 0; s < Tile<D>::KS; ++s) f[s] = *reinterpret_cast<const bf16x8 *>(base + 32 * s);
 }
 
-template <int D, bool CLAMP, bool BIDIR>
+template <int D, bool CLAMP, bool BIDIR, bool FULL>
 __global__ __launch_bounds__(NT, 2) void backward_q_bf16_kernel(BwdParams bp, int n_qt, uint32_t n_logical) {
     using T = Tile<D>;
     constexpr int KS = T::KS, DB = T::DB;
@@ -295,11 +295,17 @@ __global__ __launch_bounds__(NT, 2) void backward_q_bf16_kernel(BwdParams bp, in
     const float al = a_loc + other_half(a_loc), bl = b_loc + other_half(b_loc);
     const float ap = a_par + other_half(a_par), bpar = b_par + other_half(b_par);
     const float dg_tot = dlog_local * (al - rs * bl) + dlog_partner * (ap - rs * bpar);
-    {
+    // dims 32db + 8i + 4g + [0, 4) of dq
+    auto dq4 = [&](int db, int i) __attribute__((always_inline)) {
+        f32x4 o;
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) o[jj] = dq[db][4 * i + jj] * p.scale;
+        return o;
+    };
+    if constexpr (FULL) {
         // Whole rows: each wavefront passes its 32 rows through a private LDS
         // region and stores them 16 bytes per lane along the rows, not kept in
-        // the caches (D = 64: 66.5 -> 64.1 us at B4 H16 N4096 k128, and the
-        // whole backward's pass 179 -> 173 us; D = 128 equal).
+        // the caches.
         constexpr int P = 4 * D + 16;
         constexpr int LPR = D / 4, RPI = 64 / LPR;
         static_assert(2 * 32 * P <= (int)sizeof(TileBuf<D>), "store staging fits a tile buffer");
@@ -308,12 +314,8 @@ __global__ __launch_bounds__(NT, 2) void backward_q_bf16_kernel(BwdParams bp, in
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                f32x4 o;
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) o[jj] = dq[db][4 * i + jj] * p.scale;
-                *reinterpret_cast<f32x4 *>(reg + c * P + (32 * db + 8 * i + 4 * g) * 4) = o;
-            }
+            for (int i = 0; i < 4; ++i)
+                *reinterpret_cast<f32x4 *>(reg + c * P + (32 * db + 8 * i + 4 * g) * 4) = dq4(db, i);
         float *dqp = bp.dq + (bh * N + (q0 - p.qpos0)) * D;
 #pragma unroll
         for (int v = 0; v < 32 / RPI; ++v) {
@@ -321,6 +323,12 @@ __global__ __launch_bounds__(NT, 2) void backward_q_bf16_kernel(BwdParams bp, in
             const f32x4 o = *reinterpret_cast<const f32x4 *>(reg + r * P + ch * 16);
             if (q0 + r < NQ) __builtin_nontemporal_store(o, reinterpret_cast<f32x4 *>(dqp + (int64_t)r * D + 4 * ch));
         }
+    } else if (t_ok) {   // as it lies
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                *reinterpret_cast<f32x4 *>(bp.dq + row * D + 32 * db + 8 * i + 4 * g) = dq4(db, i);
     }
     if (t_ok) {
         if (g == 0) {
@@ -335,8 +343,16 @@ hipError_t launch_q(const BwdParams &p, hipStream_t stream) {
     const int n_qt = (p.f.N + BM - 1) / BM;
     const int64_t n_logical = (int64_t)p.f.B * p.f.H * n_qt;
     const int64_t grid = xcd_grid(n_logical);
-    return launch_kernel(backward_q_bf16_kernel<D, CLAMP, BIDIR>, dim3((unsigned)grid), dim3(NT), stream, p, n_qt,
-                         (uint32_t)n_logical);
+    // dq stored as whole rows once every CU has a work-group (pass at 512 tiles,
+    // N1000 k64: D = 64 18.7 -> 17.5 us, D = 128 28.4 -> 26.9; at B4 H16 N4096
+    // k128 59.7 -> 56.7 and 131 -> 122).  Below, one work-group's time counts
+    // and the way through LDS adds to it (64 tiles: 11.2 against 11.6 us, D =
+    // 128 15.8 against 16.5; a long band, B1 H4 N3000 k1000 bidirectionally at
+    // D = 128, 79 against 87), and with tiles of one wavefront's rows most of it
+    // is the barrier (B256 H16 N20: 30.8 against 32.8, 55 against 63).
+    const bool full = n_logical >= 256 && p.f.N > 32;
+    return launch_kernel(full ? backward_q_bf16_kernel<D, CLAMP, BIDIR, true> : backward_q_bf16_kernel<D, CLAMP, BIDIR, false>,
+                         dim3((unsigned)grid), dim3(NT), stream, p, n_qt, (uint32_t)n_logical);
 }
 
 template <int D, bool BIDIR>
