@@ -184,6 +184,7 @@ hipError_t launch_fwd(const FwdParams &p, hipStream_t stream) {
 
 hipError_t launch_forward_f32(const FwdParams &p, hipStream_t stream) {
     if ((int64_t)p.B * p.H * p.N == 0) return hipSuccess;
+    if (one_per_row(p)) return launch_forward_rows_f32(p, stream);
     return p.D == 64 ? launch_fwd<64>(p, stream) : launch_fwd<128>(p, stream);
 }
 

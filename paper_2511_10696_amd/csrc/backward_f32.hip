@@ -39,30 +39,6 @@ namespace {
 
 using namespace f32;
 
-// Prior derivatives of one gate logit (natural-log units).
-struct GateGrad {
-    float local, partner;
-};
-
-__device__ inline GateGrad gate_grad(float g) {
-    const float a = 1.0f / (1.0f + __expf(-g));
-    const float at = kGateEps + (1.0f - 2.0f * kGateEps) * a;
-    const float c = (1.0f - 2.0f * kGateEps) * a * (1.0f - a);
-    return GateGrad{c / at, -c / (1.0f - at)};
-}
-
-// alpha^ of one entry from its dot product; `cut` when the clamp saturates.
-// bias: the entry's prior; shift = (lse_shift - lse) (natural log).
-__device__ inline float weight(float dot, float bias, float shift, const FwdParams &f, bool clamp_on, bool &cut) {
-    float d = __builtin_fmaf(dot, f.scale, bias);
-    cut = false;
-    if (clamp_on) {
-        d = fminf(fmaxf(d, -f.clamp), f.clamp);
-        cut = fabsf(d) >= f.clamp;
-    }
-    return __builtin_amdgcn_exp2f((d + shift) * kLog2e);
-}
-
 // ---- query pass -----------------------------------------------------------------
 template <int D, bool SPLIT>
 __global__ __launch_bounds__(NT, D == 64 && !SPLIT ? 4 : 2) void backward_q_f32_kernel(BwdParams bp, int n_qt, uint32_t n_tiles,
@@ -142,7 +118,7 @@ __global__ __launch_bounds__(NT, D == 64 && !SPLIT ? 4 : 2) void backward_q_f32_
     }
 
 
-    const GateGrad gg = gate_grad(gl);
+    const GateDeriv gg = gate_deriv(gl);
     d_win = col_sum(d_win);
     d_par = col_sum(d_par);
     float *dqp = bp.dq + (bh * N + q0) * D;
@@ -333,6 +309,7 @@ hipError_t launch_d(const BwdParams &p, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_backward_f32(const BwdParams &p, hipStream_t stream) {
+    if (one_per_row(p.f)) return launch_backward_rows_f32(p, stream);
     return p.f.D == 64 ? launch_d<64>(p, stream) : launch_d<128>(p, stream);
 }
 

@@ -21,6 +21,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "kernels.h"
 #include "pi_common.h"
 
 namespace pi_attn {
@@ -259,6 +260,18 @@ struct Walk {
 // and 11.2, 20.2, 17.2 split; 8000 tiles of k = 64 57 alone and 75 split
 // (forward).  So: split while half the chip's 1024 SIMDs would be idle.
 constexpr int64_t kSplitTiles = 512;   // SPLIT up to here
+
+// alpha^ of one entry from its dot product; `cut` when the clamp saturates.
+// bias: the entry's prior; shift = (lse_shift - lse) (natural log).
+__device__ inline float weight(float dot, float bias, float shift, const FwdParams &f, bool clamp_on, bool &cut) {
+    float d = __builtin_fmaf(dot, f.scale, bias);
+    cut = false;
+    if (clamp_on) {
+        d = fminf(fmaxf(d, -f.clamp), f.clamp);
+        cut = fabsf(d) >= f.clamp;
+    }
+    return __builtin_amdgcn_exp2f((d + shift) * kLog2e);
+}
 
 inline int64_t tiles_of(int64_t bh, int n) { return bh * ((n + TILE - 1) / TILE); }
 

@@ -63,8 +63,11 @@ struct BwdParams {
 
 hipError_t launch_index_set(int n, int k, int pi, bool causal, int32_t *idx, hipStream_t stream);
 
-// float32 forward on MFMA tiles of 16 queries (D = 64 or 128).
+// float32 forward (D = 64 or 128): MFMA tiles of 16 queries, or one wavefront
+// per query where one_per_row().
+bool one_per_row(const FwdParams &p);
 hipError_t launch_forward_f32(const FwdParams &p, hipStream_t stream);
+hipError_t launch_forward_rows_f32(const FwdParams &p, hipStream_t stream);
 
 // bf16 banded MFMA forward (D = 64 or 128).
 hipError_t launch_forward_bf16(const FwdParams &p, hipStream_t stream);
@@ -79,8 +82,9 @@ hipError_t launch_backward(const BwdParams &p, hipStream_t stream);
 // out[h] = sum over b and t of dgate[b][h][t] (fixed order, fp64 sums).
 hipError_t launch_gate_grad_per_head(int B, int H, int N, const float *dgate, float *out, hipStream_t stream);
 
-// Both passes for float32 data.
+// Both passes for float32 data, the same two ways.
 hipError_t launch_backward_f32(const BwdParams &p, hipStream_t stream);
+hipError_t launch_backward_rows_f32(const BwdParams &p, hipStream_t stream);
 
 // MFMA query pass (dq, dgate, row terms) for bf16 inputs.
 hipError_t launch_backward_q_bf16(const BwdParams &p, hipStream_t stream);

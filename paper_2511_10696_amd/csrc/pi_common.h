@@ -88,6 +88,18 @@ __device__ inline FusionBias fusion_bias(float g, bool exact) {
     return fb;
 }
 
+// Prior derivatives of one gate logit: d log alpha~/dg and d log(1 - alpha~)/dg.
+struct GateDeriv {
+    float local, partner;
+};
+
+__device__ inline GateDeriv gate_deriv(float g) {
+    const float a = 1.0f / (1.0f + __expf(-g));
+    const float at = kGateEps + (1.0f - 2.0f * kGateEps) * a;
+    const float c = (1.0f - 2.0f * kGateEps) * a * (1.0f - a);
+    return GateDeriv{c / at, -c / (1.0f - at)};
+}
+
 // XCD-aware work-group order.  Consecutive work-group ids are dispatched
 // round-robin over the 8 XCDs; this remaps them so that each XCD receives a
 // contiguous range of logical tiles (neighbouring query tiles share most of

@@ -76,18 +76,6 @@ __device__ inline void axpy8(float *acc, float p, const uint4 &v) {
     }
 }
 
-// Prior derivatives of one gate logit: d log alpha~/dg and d log(1 - alpha~)/dg.
-struct GateDeriv {
-    float local, partner;
-};
-
-__device__ inline GateDeriv gate_deriv(float g) {
-    const float a = 1.0f / (1.0f + __expf(-g));
-    const float at = kGateEps + (1.0f - 2.0f * kGateEps) * a;
-    const float c = (1.0f - 2.0f * kGateEps) * a * (1.0f - a);
-    return GateDeriv{c / at, -c / (1.0f - at)};
-}
-
 // Fused logit in log2 units of one entry from its dot product: clamped with
 // the exact prior, or shifted (see fusion_bias); `cut` when it saturates.
 __device__ inline float logit2(float dot, float bias, const FwdParams &f, bool clamp_on, bool &cut) {
