@@ -8,7 +8,8 @@ library is missing or the tensors are not on the GPU, the calls raise.
 The forward, the gated forward, the backward and the decode step marshal
 their plain calls in native code (``csrc/binding.cpp``), which returns None
 for anything unusual or wrong before it enqueues anything; the Python code
-below it then serves the call, or says what is wrong with it.
+below it then serves the call, or says what is wrong with it.  A launch that
+the HIP runtime refuses is an error at once, in native code too.
 
 Entry points (same names as the C ABI; ``causal=False`` selects the
 bidirectional mode, window |j - t| <= k and partners t -/+ pi):

@@ -12,7 +12,9 @@
 // another type, another device, a tensor subclass or a wrapped tensor, an
 // active torch function or dispatch mode, a given stream, an argument that
 // the checks or the library refuse -- it returns None before anything is
-// enqueued, and the Python code handles the call (and words the error).
+// enqueued, and the Python code handles the call (and words the error).  A
+// launch that the HIP runtime refuses (PI_ATTN_EHIP) raises PiAttnError here:
+// of a call of several launches the first ones may be enqueued by then.
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -24,6 +26,7 @@
 
 #include <array>
 #include <cmath>
+#include <string>
 
 #include "pi_attn.h"
 
@@ -163,8 +166,17 @@ PyObject *pack(std::initializer_list<Tensor> ts) {
     return r;
 }
 
+// The result of a call whose status is not PI_ATTN_OK.
+PyObject *refused(PyObject *self, int status, const char *where) {
+    if (status != PI_ATTN_EHIP) Py_RETURN_NONE;
+    const auto package = pybind11::handle(self).attr("__package__");
+    const auto error = pybind11::module_::import(pybind11::str(package).cast<std::string>().c_str()).attr("PiAttnError");
+    PyErr_SetObject(error.ptr(), error(status, where).ptr());
+    return nullptr;
+}
+
 // q, k, v, gate, k_window, pi, scale, logit_clamp, out, return_lse, lse, stream, causal
-PyObject *forward(PyObject *, PyObject *const *args, Py_ssize_t n) {
+PyObject *forward(PyObject *self, PyObject *const *args, Py_ssize_t n) {
     HANDLE_TH_ERRORS
     Args a(args, n, 13);
     const Tensor q = a.tensor(), k = a.tensor(), v = a.tensor(), gate = a.tensor();
@@ -181,22 +193,22 @@ PyObject *forward(PyObject *, PyObject *const *args, Py_ssize_t n) {
     bool per_query;
     if (!a.ok || !gate_strides(gate, s, gs, per_query)) Py_RETURN_NONE;
     const bool with_lse = want_lse || lse.defined();
-    bool done = false;
+    int status = PI_ATTN_EINVAL;
     {
         pybind11::gil_scoped_release no_gil;
-        done = like_out(out, q) && (!with_lse || f32_out(lse, {s.B, s.H, s.N}, a.device)) &&
-               pi_attn_forward(dtype_of(q), s.B, s.H, s.N, s.D, kw, pi, causal, q.data_ptr(), k.data_ptr(),
-                               v.data_ptr(), q.stride(0), q.stride(1), q.stride(2), ptr<float>(gate), gs[0], gs[1],
-                               gs[2], scale, clamp, out.data_ptr(), out.stride(0), out.stride(1), out.stride(2),
-                               ptr<float>(lse), stream_of(a.device)) == PI_ATTN_OK;
+        if (like_out(out, q) && (!with_lse || f32_out(lse, {s.B, s.H, s.N}, a.device)))
+            status = pi_attn_forward(dtype_of(q), s.B, s.H, s.N, s.D, kw, pi, causal, q.data_ptr(), k.data_ptr(),
+                                     v.data_ptr(), q.stride(0), q.stride(1), q.stride(2), ptr<float>(gate), gs[0],
+                                     gs[1], gs[2], scale, clamp, out.data_ptr(), out.stride(0), out.stride(1),
+                                     out.stride(2), ptr<float>(lse), stream_of(a.device));
     }
-    if (!done) Py_RETURN_NONE;
+    if (status != PI_ATTN_OK) return refused(self, status, "pi_attn_forward");
     return with_lse ? pack({out, lse}) : THPVariable_Wrap(out);
     END_HANDLE_TH_ERRORS
 }
 
 // q, k, v, u, w2, b2, k_window, pi, scale, logit_clamp, out, return_lse, lse, gate_out, stream, causal
-PyObject *forward_gated(PyObject *, PyObject *const *args, Py_ssize_t n) {
+PyObject *forward_gated(PyObject *self, PyObject *const *args, Py_ssize_t n) {
     HANDLE_TH_ERRORS
     Args a(args, n, 16);
     const Tensor q = a.tensor(), k = a.tensor(), v = a.tensor(), u = a.tensor(), w2 = a.tensor();
@@ -216,25 +228,25 @@ PyObject *forward_gated(PyObject *, PyObject *const *args, Py_ssize_t n) {
     if (dh > INT32_MAX || w2.sizes() != at::IntArrayRef({s.H, dh}) || !w2.is_contiguous()) Py_RETURN_NONE;
     if (b2.defined() && !is_f32(b2, {s.H})) Py_RETURN_NONE;
     const bool with_lse = want_lse || lse.defined();
-    bool done = false;
+    int status = PI_ATTN_EINVAL;
     {
         pybind11::gil_scoped_release no_gil;
-        done = like_out(out, q) && f32_out(gate, {s.B, s.H, s.N}, a.device) &&
-               (!with_lse || f32_out(lse, {s.B, s.H, s.N}, a.device)) &&
-               pi_attn_forward_gated(dtype_of(q), s.B, s.H, s.N, s.D, kw, pi, causal, q.data_ptr(), k.data_ptr(),
-                                     v.data_ptr(), q.stride(0), q.stride(1), q.stride(2), u.data_ptr(), u.stride(0),
-                                     u.stride(1), dh, w2.data_ptr(), ptr<float>(b2), scale, clamp, out.data_ptr(),
-                                     out.stride(0), out.stride(1), out.stride(2), ptr<float>(lse), ptr<float>(gate),
-                                     stream_of(a.device)) == PI_ATTN_OK;
+        if (like_out(out, q) && f32_out(gate, {s.B, s.H, s.N}, a.device) &&
+            (!with_lse || f32_out(lse, {s.B, s.H, s.N}, a.device)))
+            status = pi_attn_forward_gated(dtype_of(q), s.B, s.H, s.N, s.D, kw, pi, causal, q.data_ptr(), k.data_ptr(),
+                                           v.data_ptr(), q.stride(0), q.stride(1), q.stride(2), u.data_ptr(),
+                                           u.stride(0), u.stride(1), dh, w2.data_ptr(), ptr<float>(b2), scale, clamp,
+                                           out.data_ptr(), out.stride(0), out.stride(1), out.stride(2), ptr<float>(lse),
+                                           ptr<float>(gate), stream_of(a.device));
     }
-    if (!done) Py_RETURN_NONE;
+    if (status != PI_ATTN_OK) return refused(self, status, "pi_attn_forward_gated");
     return with_lse ? pack({out, gate, lse}) : pack({out, gate});
     END_HANDLE_TH_ERRORS
 }
 
 // q, k, v, gate, k_window, pi, out, lse, dout, scale, logit_clamp, gate_grad_per_query, stream, causal, dq, dk, dv,
 // dgate, rowterm
-PyObject *backward(PyObject *, PyObject *const *args, Py_ssize_t n) {
+PyObject *backward(PyObject *self, PyObject *const *args, Py_ssize_t n) {
     HANDLE_TH_ERRORS
     Args a(args, n, 19);
     const Tensor q = a.tensor(), k = a.tensor(), v = a.tensor(), gate = a.tensor();
@@ -254,31 +266,33 @@ PyObject *backward(PyObject *, PyObject *const *args, Py_ssize_t n) {
         out.sizes() != q.sizes() || dout.stride(3) != 1 || !is_f32(lse, {s.B, s.H, s.N}))
         Py_RETURN_NONE;
     Tensor per_head;
-    bool done = false;
+    int status = PI_ATTN_EINVAL;
+    const char *where = "pi_attn_backward";
     {
         pybind11::gil_scoped_release no_gil;
         const std::array<int64_t, 4> full{s.B, s.H, s.N, s.D};
         const std::array<int64_t, 3> rows{s.B, s.H, s.N};
-        done = f32_out(dq, full, a.device) && f32_out(dk, full, a.device) && f32_out(dv, full, a.device) &&
-               f32_out(dg, rows, a.device) && f32_out(rt, rows, a.device);
         void *stream = stream_of(a.device);
-        done = done && pi_attn_backward(dtype_of(q), s.B, s.H, s.N, s.D, kw, pi, causal, q.data_ptr(), k.data_ptr(),
-                                        v.data_ptr(), q.stride(0), q.stride(1), q.stride(2), ptr<float>(gate), gs[0],
-                                        gs[1], gs[2], scale, clamp, ptr<float>(lse), out.data_ptr(), dout.data_ptr(),
-                                        dout.stride(0), dout.stride(1), dout.stride(2), ptr<float>(dq), ptr<float>(dk),
-                                        ptr<float>(dv), ptr<float>(dg), ptr<float>(rt), stream) == PI_ATTN_OK;
-        if (done && !per_query && !keep_per_query) {
+        if (f32_out(dq, full, a.device) && f32_out(dk, full, a.device) && f32_out(dv, full, a.device) &&
+            f32_out(dg, rows, a.device) && f32_out(rt, rows, a.device))
+            status = pi_attn_backward(dtype_of(q), s.B, s.H, s.N, s.D, kw, pi, causal, q.data_ptr(), k.data_ptr(),
+                                      v.data_ptr(), q.stride(0), q.stride(1), q.stride(2), ptr<float>(gate), gs[0],
+                                      gs[1], gs[2], scale, clamp, ptr<float>(lse), out.data_ptr(), dout.data_ptr(),
+                                      dout.stride(0), dout.stride(1), dout.stride(2), ptr<float>(dq), ptr<float>(dk),
+                                      ptr<float>(dv), ptr<float>(dg), ptr<float>(rt), stream);
+        if (status == PI_ATTN_OK && !per_query && !keep_per_query) {
+            where = "pi_attn_gate_grad_per_head";   // of valid arguments: refused by the runtime or not at all
             f32_out(per_head, {s.H}, a.device);
-            done = pi_attn_gate_grad_per_head(s.B, s.H, s.N, ptr<float>(dg), ptr<float>(per_head), stream) == PI_ATTN_OK;
+            status = pi_attn_gate_grad_per_head(s.B, s.H, s.N, ptr<float>(dg), ptr<float>(per_head), stream);
         }
     }
-    if (!done) Py_RETURN_NONE;
+    if (status != PI_ATTN_OK) return refused(self, status, where);
     return pack({dq, dk, dv, per_head.defined() ? per_head : dg});
     END_HANDLE_TH_ERRORS
 }
 
 // len_in, q_new, k_new, v_new, k_cache, v_cache, gate, k, pi, scale, logit_clamp, len_out, out, lse, stream
-PyObject *decode_step(PyObject *, PyObject *const *args, Py_ssize_t n) {
+PyObject *decode_step(PyObject *self, PyObject *const *args, Py_ssize_t n) {
     HANDLE_TH_ERRORS
     Args a(args, n, 15);
     const Tensor len_in = a.tensor(), q = a.tensor(), k = a.tensor(), v = a.tensor(), kc = a.tensor(),
@@ -314,16 +328,16 @@ PyObject *decode_step(PyObject *, PyObject *const *args, Py_ssize_t n) {
         Py_RETURN_NONE;
     }
     if ((out.defined() && !cached(out, rows)) || (lse.defined() && !is_f32(lse, {S, H}))) Py_RETURN_NONE;
-    bool done = false;
+    int status;
     {
         pybind11::gil_scoped_release no_gil;
         if (!out.defined()) out = at::empty(rows, at::TensorOptions().dtype(kc.scalar_type()).device(a.device));
-        done = pi_attn_decode_step(dtype_of(kc), S, H, D, cap, kw, pi, ptr<int32_t>(len_in), ptr<int32_t>(len_out),
-                                   q.data_ptr(), k.data_ptr(), v.data_ptr(), kc.data_ptr(), vc.data_ptr(),
-                                   ptr<float>(gate), gss, gsh, scale, clamp, out.data_ptr(), ptr<float>(lse),
-                                   stream_of(a.device)) == PI_ATTN_OK;
+        status = pi_attn_decode_step(dtype_of(kc), S, H, D, cap, kw, pi, ptr<int32_t>(len_in), ptr<int32_t>(len_out),
+                                     q.data_ptr(), k.data_ptr(), v.data_ptr(), kc.data_ptr(), vc.data_ptr(),
+                                     ptr<float>(gate), gss, gsh, scale, clamp, out.data_ptr(), ptr<float>(lse),
+                                     stream_of(a.device));
     }
-    if (!done) Py_RETURN_NONE;
+    if (status != PI_ATTN_OK) return refused(self, status, "pi_attn_decode_step");
     return THPVariable_Wrap(out);
     END_HANDLE_TH_ERRORS
 }

@@ -171,3 +171,20 @@ def test_streams_threads_and_graphs(device):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, pa.pi_attn_forward(q, kk, v, g, 20, 30))
+
+
+def test_refused_launch_is_not_repeated(device, monkeypatch):
+    """A launch that the HIP runtime refuses -- 2^24 work-groups of 256 -- ends
+    the call in the native code: the Python code does not issue it again."""
+    B, H = 1 << 20, 16
+    q, kk, v = (rnd(1, 1, 1, 64, seed=i).expand(B, H, 1, 64) for i in range(3))
+    entered = []
+    monkeypatch.setattr(pa, "_stream_handle", lambda *a: entered.append(a))
+    with pytest.raises(pa.PiAttnError, match="^pi_attn_forward: ") as e:
+        pa.pi_attn_forward(q, kk, v, rnd(H, dtype=torch.float32), 17, 20)
+    assert e.value.status == -3 and not entered
+    try:   # the runtime's last error, which the next launch of torch reports
+        torch.zeros(1, device="cuda")
+    except RuntimeError:
+        pass
+    torch.cuda.synchronize()
