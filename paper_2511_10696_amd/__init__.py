@@ -102,16 +102,29 @@ def library() -> ctypes.CDLL:
     return _lib
 
 
+class _PythonOnly:
+    """Stands in for _binding where only the library is built: no call is
+    plain, the Python code serves them all (with some 10 us more of host
+    time each)."""
+
+    @staticmethod
+    def forward(*args):
+        return None
+
+    forward_gated = backward = decode_step = forward
+
+
 def _load_native():
-    """Load _binding.so (and with it torch), built beside the library."""
+    """Load _binding.so (and with it torch), if it is built beside the library."""
     global _native
     library()
-    if not os.path.exists(BINDING_PATH):
-        raise RuntimeError(f"{BINDING_PATH} is not built; run `python -m paper_2511_10696_amd.build`")
-    import torch  # noqa: F401  (its libraries resolve the module's symbols)
-    from . import _binding
-    _native = _binding
-    return _binding
+    if os.path.exists(BINDING_PATH):
+        import torch  # noqa: F401  (its libraries resolve the module's symbols)
+        from . import _binding
+        _native = _binding
+    else:
+        _native = _PythonOnly
+    return _native
 
 
 def pi_attn_strerror(status: int) -> str:

@@ -5,11 +5,14 @@
 Each ``csrc/*.hip`` is compiled to an object under ``_build/`` (in parallel)
 and linked into ``paper_2511_10696_amd/libpi_attn.so``; ``csrc/binding.cpp``,
 the native marshalling of torch tensors, becomes
-``paper_2511_10696_amd/_binding.so`` beside it.
+``paper_2511_10696_amd/_binding.so`` beside it.  The library needs neither
+torch nor Python's headers; where they are missing it is built alone, and the
+Python code marshals every call.
 """
 from __future__ import annotations
 
 import glob
+import importlib.util
 import os
 import re
 import subprocess
@@ -76,10 +79,20 @@ def _compile(src: str) -> str:
     return obj
 
 
-def _build_binding() -> None:
+def _torch_init() -> str | None:
+    """torch/__init__.py, if the binding can be built here: its C++ API and
+    Python's headers are there."""
+    spec = importlib.util.find_spec("torch")
+    if spec is None or spec.origin is None:
+        return None
+    needed = [os.path.join(os.path.dirname(spec.origin), "include", "torch", "csrc", "Exceptions.h"),
+              os.path.join(sysconfig.get_paths()["include"], "Python.h")]
+    return spec.origin if all(map(os.path.exists, needed)) else None
+
+
+def _build_binding(torch_init: str) -> None:
     """_binding.so: host code against torch's C++ API and libpi_attn.so."""
-    import torch
-    tdir = os.path.dirname(torch.__file__)
+    tdir = os.path.dirname(torch_init)
     includes = [os.path.join(tdir, "include"), os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
                 sysconfig.get_paths()["include"], os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include")]
     tmp = BINDING_PATH + ".tmp"
@@ -107,9 +120,14 @@ def build(verbose: bool = False) -> str:
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
     os.replace(tmp, LIB_PATH)
-    _build_binding()
+    torch_init = _torch_init()
+    if torch_init:
+        _build_binding(torch_init)
+    elif os.path.exists(BINDING_PATH):   # of another library
+        os.remove(BINDING_PATH)
     if verbose:
-        print(f"built {LIB_PATH} and {BINDING_PATH}")
+        print(f"built {LIB_PATH}" + (f" and {BINDING_PATH}" if torch_init else
+                                     "; no torch or Python headers: without the native marshalling"))
     return LIB_PATH
 
 

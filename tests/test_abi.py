@@ -389,3 +389,34 @@ def test_native_marshalling_declines_what_is_not_plain(lib):
     assert native.forward(x, x, x, g, 2, 4, None, 0.0, None, False, None, None, True) is None
     assert native.forward() is None and native.decode_step(1, 2, 3) is None
     assert native.backward(*[None] * 19) is None and native.forward_gated(*[3.0] * 16) is None
+
+
+def test_library_without_native_marshalling(lib, monkeypatch, tmp_path):
+    """Where only the library is built the Python code serves the calls."""
+    import torch
+    monkeypatch.setattr(pa, "BINDING_PATH", str(tmp_path / "_binding.so"))
+    monkeypatch.setattr(pa, "_native", None)
+    q = torch.zeros(1, 1, 4, 64)
+    with pytest.raises(RuntimeError, match="must be on the GPU"):
+        pa.pi_attn_forward(q, q, q, torch.zeros(1), 2, 4)
+    native = pa._native
+    assert native is not None and all(f() is None for f in (native.forward, native.forward_gated, native.backward,
+                                                            native.decode_step))
+
+
+def test_build_without_torch(monkeypatch, tmp_path):
+    """The library is built where torch is missing, and a _binding.so of
+    another build does not stay beside it."""
+    import sys
+
+    from paper_2511_10696_amd import build
+    source = tmp_path / "one.hip"
+    source.write_text('extern "C" int pi_attn_one() { return 1; }\n')
+    monkeypatch.setattr(build, "sources", lambda: [str(source)])
+    for name, file in (("BUILD_DIR", "_build"), ("LIB_PATH", "libpi_attn.so"), ("BINDING_PATH", "_binding.so")):
+        monkeypatch.setattr(build, name, str(tmp_path / file))
+    monkeypatch.setitem(sys.modules, "torch", None)
+    (tmp_path / "_binding.so").write_bytes(b"")
+    assert build.build() == str(tmp_path / "libpi_attn.so")
+    assert ctypes.CDLL(build.LIB_PATH).pi_attn_one() == 1
+    assert not os.path.exists(build.BINDING_PATH)
