@@ -35,6 +35,7 @@
 // barrier: S and dP, then dV and dK; alpha^ is double-buffered by block.
 #include <algorithm>
 
+#include "bwd_tile.h"
 #include "kernels.h"
 #include "pi_common.h"
 
@@ -42,12 +43,7 @@ namespace pi_attn {
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+using bwd::chunk_x;
 
 constexpr int PAIRS = 4;
 constexpr int NT = 64 * 2 * PAIRS;
@@ -88,32 +84,6 @@ struct Stage {
     float gl, lse, r;   // raw per-row values: gate logit, lse, row term
     bool band;          // a window-band row (else a partner-run row)
 };
-
-// LDS layout of the Q and dL/dy tiles: rows padded by 64 bytes, and the low
-// two bits of a row's 16-byte chunk index XORed with bits 2-3 of the row.
-// Both reads of a tile are then free of bank conflicts: the row fragments
-// (16 consecutive rows, one chunk each) and the transpose reads (4
-// consecutive rows, 4 consecutive chunks each); the offsets stay affine in
-// the k-step (two bases, even and odd steps) and in the dimension block.
-__device__ inline int chunk_x(int row) { return (row >> 2) & 3; }
-
-// The value held by the other half of the wavefront (lane l ^ 32).
-__device__ inline float other_half(float x) {
-    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(__lane_id() < 32 ? p[1] : p[0]);
-}
-
-// acc + <a, b> over eight bf16 pairs (packed products, fp32 sums).
-__device__ inline float dot_bf16x8(const bf16x8 &a, const bf16x8 &b, float acc) {
-    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 0, 1), __builtin_shufflevector(b, b, 0, 1),
-                                          acc, false);
-    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 2, 3), __builtin_shufflevector(b, b, 2, 3),
-                                          acc, false);
-    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 4, 5), __builtin_shufflevector(b, b, 4, 5),
-                                          acc, false);
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 6, 7), __builtin_shufflevector(b, b, 6, 7),
-                                           acc, false);
-}
 
 template <int D, bool CLAMP, bool BIDIR>
 __global__ __launch_bounds__(NT) void backward_kv_bf16_kernel(BwdParams bp, int n_kt, uint32_t n_logical) {

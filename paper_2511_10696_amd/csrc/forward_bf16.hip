@@ -61,6 +61,7 @@
 // path).
 #include <algorithm>
 
+#include "bf16_rows.h"
 #include "kernels.h"
 #include "pi_common.h"
 
@@ -68,12 +69,7 @@ namespace pi_attn {
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 constexpr int WAVES = 4;
 constexpr int NT = 64 * WAVES;   // threads per work-group
@@ -146,12 +142,6 @@ __device__ inline void tile_fetch(TileBuf<D> &tb, u32x4 rk, u32x4 rv, int rowb, 
     }
 }
 
-// The value held by the other half of the wavefront (lane l ^ 32).
-__device__ inline float other_half(float x) {
-    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(__lane_id() < 32 ? p[1] : p[0]);
-}
-
 __device__ inline float max16(const f32x16 &a) {
     float m0 = fmaxf(fmaxf(a[0], a[1]), a[2]), m1 = fmaxf(fmaxf(a[3], a[4]), a[5]);
     float m2 = fmaxf(fmaxf(a[6], a[7]), a[8]), m3 = fmaxf(fmaxf(a[9], a[10]), a[11]);
@@ -179,18 +169,6 @@ __device__ inline float sum_bf16x8(const bf16x8 &p, float s) {
     s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(p, p, 4, 5), one, s, false);
     s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(p, p, 6, 7), one, s, false);
     return s;
-}
-
-// acc + <a, b> over eight bf16 pairs (packed products, fp32 sums).
-__device__ inline float dot_bf16x8(const bf16x8 &a, const bf16x8 &b, float acc) {
-    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 0, 1), __builtin_shufflevector(b, b, 0, 1),
-                                          acc, false);
-    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 2, 3), __builtin_shufflevector(b, b, 2, 3),
-                                          acc, false);
-    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 4, 5), __builtin_shufflevector(b, b, 4, 5),
-                                          acc, false);
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 6, 7), __builtin_shufflevector(b, b, 6, 7),
-                                           acc, false);
 }
 
 // Scores of one 32-key block -> log2-unit logits (masked to -inf on edge
@@ -405,22 +383,8 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void forward_bf16_kernel(FwdPa
     ws.lb = ws.l;   // the partner weights enter the accumulator unrounded
     // Lanes without that partner contribute exactly 0 (their loads read a
     // clamped row whose data is not used, not even multiplied by 0).
-    // The value row in the accumulator layout: the 8-dim group m = 4db + i,
-    // of which this lane needs dims 4g..4g+3, is held whole by lane
-    // (c, m & 1) in vf[m >> 1]; each lane keeps its own half of its groups
-    // and takes the other half from the other half of the wavefront.
     auto seed_layout = [&](const bf16x8 (&vf)[W::KS], uint2 (&vr)[W::DB][4]) {
-#pragma unroll
-        for (int s2 = 0; s2 < W::KS; ++s2) {
-            const uint4 own = __builtin_bit_cast(uint4, vf[s2]);
-            // lane g = 0 sends dims 4..7 of its group, lane g = 1 dims 0..3
-            const uint2 send = g == 0 ? make_uint2(own.z, own.w) : make_uint2(own.x, own.y);
-            const uint2 recv = make_uint2(__float_as_uint(other_half(__uint_as_float(send.x))),
-                                          __float_as_uint(other_half(__uint_as_float(send.y))));
-            const int m0 = 2 * s2, m1 = 2 * s2 + 1;
-            vr[m0 >> 2][m0 & 3] = g == 0 ? make_uint2(own.x, own.y) : recv;
-            vr[m1 >> 2][m1 & 3] = g == 0 ? recv : make_uint2(own.z, own.w);
-        }
+        regroup_row(vf, g, [&](int db, int i, uint2 raw) __attribute__((always_inline)) { vr[db][i] = raw; });
     };
     auto seed = [&](uint2 (&vr)[W::DB][4], float wt, bool has, bool add) {
 #pragma unroll
