@@ -53,12 +53,12 @@ SMALLK_TRAFFIC = {"gated": os.path.join(ROOT, "profiles", "smallk_bf16_gated_sma
                   "backward": os.path.join(ROOT, "profiles", "smallk_bwd_bf16_smallk8k_counters.txt"),
                   "backward_bidirectional": os.path.join(ROOT, "profiles",
                                                          "smallk_bwd_bf16_bidir_smallk8k_counters.txt")}
-FORWARD_SOURCES = ("forward_bf16.hip", "pi_common.h", "kernels.h")
+FORWARD_SOURCES = ("forward_bf16.hip", "bf16_rows.h", "pi_common.h", "kernels.h")
 SMALLK_SOURCES = ("smallk_bf16.hip", "smallk_common.h", "smallk.h", "pi_common.h", "kernels.h")
 SMALLK_BWD_SOURCES = ("smallk_bwd_fused_bf16.hip", "smallk_bwd_bf16.hip", "smallk_common.h", "smallk.h",
                       "backward.hip", "pi_common.h", "kernels.h")
-BACKWARD_SOURCES = ("backward_bf16.hip", "backward_kv_bf16.hip", "bwd_tile.h", "backward.hip", "pi_common.h",
-                    "kernels.h")
+BACKWARD_SOURCES = ("backward_bf16.hip", "backward_kv_bf16.hip", "bwd_tile.h", "bf16_rows.h", "backward.hip",
+                    "pi_common.h", "kernels.h")
 DECODE_SOURCES = ("decode.hip", "pi_common.h", "kernels.h")
 
 

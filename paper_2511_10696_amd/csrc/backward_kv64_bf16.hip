@@ -302,7 +302,7 @@ __global__ __launch_bounds__(NT, 2) void backward_kv64_bf16_kernel(BwdParams bp,
     // region (the tile buffers, free once every wavefront has left the loop)
     // and stores 256 contiguous bytes per row, 16 bytes per lane, not kept in
     // the caches (a training pass at B4 H16 N4096 k128: 173 -> 167 us).
-    constexpr int P = 4 * D + 16;   // LDS row pitch (bytes), padded against bank conflicts
+    constexpr int P = 4 * D + 16;   // LDS row pitch (bytes): rows shifted by 4 of the 64 banks, as unpadded ones all meet
     static_assert(2 * 32 * P <= (int)sizeof(TileBuf), "store staging fits a tile buffer");
     __syncthreads();
     unsigned char *reg = reinterpret_cast<unsigned char *>(w < 2 ? &tA : &tB) + (w & 1) * 32 * P;

@@ -452,7 +452,7 @@ __global__ __launch_bounds__(NT) void backward_kv_bf16_kernel(BwdParams bp, int 
     // instead of 16-byte pieces of 32 rows per instruction.
     {
         constexpr int HW = D / 2;              // dims per pass
-        constexpr int P = HW * 4 + 16;         // LDS row pitch (bytes), padded against bank conflicts
+        constexpr int P = HW * 4 + 16;         // LDS row pitch (bytes): rows shifted by 4 of the 64 banks
         constexpr int LPR = HW / 4;            // lanes per row when reading back
         constexpr int RPI = 64 / LPR;          // rows per read instruction
         static_assert(4 * 32 * P <= (int)sizeof(QTile<D>), "store staging fits a tile buffer");
