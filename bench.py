@@ -395,7 +395,7 @@ def main():
                                   args.cold_reps, stream)
     keys, flops, nbytes = forward_algorithmic(cfg)
     digest = csrc_digest(FORWARD_SOURCES)
-    roofline, roofline_mfma = roofline_of(flops, nbytes, sec, "forward_bf16_kernel<128,false,false,false,true>",
+    roofline, roofline_mfma = roofline_of(flops, nbytes, sec, "forward_bf16_kernel<128,false,false,false,true,false>",
                                           measured_traffic(digest), measured_counters(digest, PROFILE_TRAFFIC, sec))
     host_inputs = [x.cpu() for x in (q, k, v, gate)]   # the exact bytes the kernel consumed, for the CPU baseline
 
@@ -406,7 +406,7 @@ def main():
             torch, lambda: pa.pi_attn_forward(q, k, v, gate, cfg.k, cfg.pi, out=out, causal=False),
             args.steps, args.warmup, stream)
         bkeys, bflops, bbytes = forward_algorithmic(cfg, causal=False)
-        brl, bmf = roofline_of(bflops, bbytes, bms / 1e3, "forward_bf16_kernel<128,false,true,false,true>",
+        brl, bmf = roofline_of(bflops, bbytes, bms / 1e3, "forward_bf16_kernel<128,false,true,false,true,false>",
                                measured_traffic(digest, BIDIR_TRAFFIC),
                                measured_counters(digest, BIDIR_TRAFFIC, bms / 1e3))
         bidir = {"workload": "fwd32k bidirectional: B1 H32 N32768 D128 k512 pi1024 bf16 (window |j-t|<=k, "
@@ -425,7 +425,7 @@ def main():
             vms, _, _ = time_launches(torch, lambda: pa.pi_attn_forward(q, k, v, gate, kk, pp, out=out), steps,
                                       1, stream)
             vkeys, vflops, vbytes = forward_algorithmic(vcfg)
-            vrl, vmf = roofline_of(vflops, vbytes, vms / 1e3, "forward_bf16_kernel<128,false,false,false,true>")
+            vrl, vmf = roofline_of(vflops, vbytes, vms / 1e3, "forward_bf16_kernel<128,false,false,false,true,false>")
             variants[name] = {"workload": f"fwd32k shape, causal, k={kk} pi={pp}", "steps": steps,
                               "ms_per_step": round(vms, 5),
                               "query_positions_per_s": round(cfg.B * cfg.N / (vms / 1e3), 1),
@@ -442,7 +442,9 @@ def main():
             cms, _, _ = time_launches(torch, cfn, args.steps, args.warmup, stream)
             ccold, ccold_min = time_cold(torch, cfn, args.cold_reps, stream)
             ckeys, cflops, cbytes = forward_algorithmic(ccfg)
-            crl, cmf = roofline_of(cflops, cbytes, cms / 1e3, f"forward_bf16_kernel<{ccfg.D},false,false,false,true>")
+            heads_first = "true" if ccfg.D == 64 else "false"
+            crl, cmf = roofline_of(cflops, cbytes, cms / 1e3,
+                                   f"forward_bf16_kernel<{ccfg.D},false,false,false,true,{heads_first}>")
             variants[cname] = {"workload": f"{cname}: causal B{ccfg.B} H{ccfg.H} N{ccfg.N} D{ccfg.D} k{ccfg.k} "
                                            f"pi{ccfg.pi} bf16", "steps": args.steps, "ms_per_step": round(cms, 5),
                                "query_positions_per_s": round(ccfg.B * ccfg.N / (cms / 1e3), 1),
@@ -519,7 +521,7 @@ def main():
                   "us_per_step_p50": round(per[len(per) // 2] * 1e3, 2),
                   "us_per_step_p99": round(per[min(len(per) - 1, (99 * len(per)) // 100)] * 1e3, 2),
                   "queries_per_s": round(dcfg.S / (dms / 1e3), 1),
-                  "roofline": {"bound": "hbm", "kernel": "decode_kernel<bf16, 128>",
+                  "roofline": {"bound": "hbm", "kernel": "decode_kernel<bf16,128,false,8,8,true>",
                                "achieved": round(dgbs, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                "frac": round(dgbs / HBM_PEAK_GBS, 4), "bytes_per_step": dbytes,
                                "traffic": dtraffic, **dcounters}}
@@ -643,7 +645,7 @@ def bench_shard(cfg, W, pa, torch, dev, stream, steps, warmup, nshard=8, rank=6)
         torch, lambda: pa.pi_attn_forward_shard(qs, ks, vs, gate, cfg.k, cfg.pi, n, s0, lo, out=out),
         steps, warmup, stream)
     keys, flops, nbytes = shard_algorithmic(cfg, s0, s1, lo)
-    rl, mf = roofline_of(flops, nbytes, ms / 1e3, "forward_bf16_kernel<128,false,false,false,true> (one shard)")
+    rl, mf = roofline_of(flops, nbytes, ms / 1e3, "forward_bf16_kernel<128,false,false,false,true,false> (one shard)")
     res = {"workload": (f"fwd32k sequence-sharded {nshard} ways, rank {rank}'s share: queries [{s0}, {s1}), "
                         f"k/v rows [{lo}, {s1}) (its own and the pi = {cfg.pi} halo rows), B1 H32 D128 k512"),
            "steps": steps, "us_per_step": round(ms * 1e3, 2),
@@ -685,7 +687,7 @@ def bench_backward(cfg, W, pa, torch, dev, stream, steps, causal):
     del q, k, v, out, dout, lse
     torch.cuda.empty_cache()
     mode = "false" if causal else "true"
-    kernels = f"backward_q_bf16_kernel<128,false,{mode}> + backward_kv_bf16_kernel<128,false,{mode}>"
+    kernels = f"backward_q_bf16_kernel<128,false,{mode},true> + backward_kv_bf16_kernel<128,false,{mode}>"
     rl, mf = roofline_of(flops, nbytes, ms / 1e3, kernels,
                          measured_traffic(csrc_digest(BACKWARD_SOURCES), BACKWARD_TRAFFIC[causal]),
                          measured_counters(csrc_digest(BACKWARD_SOURCES), BACKWARD_TRAFFIC[causal], ms / 1e3))
