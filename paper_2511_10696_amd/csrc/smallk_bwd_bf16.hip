@@ -23,6 +23,8 @@
 // and the partner queries t = j + pi (bidirectional also j - pi), read from
 // global memory:
 //   dk_j = scale sum_t ddelta_tj q_t,   dv_j = sum_t alpha^_tj dL/dy_t.
+#include <algorithm>
+
 #include "kernels.h"
 #include "pi_common.h"
 #include "smallk.h"
@@ -221,7 +223,8 @@ __global__ __launch_bounds__(NT) void smallk_bwd_q_kernel(BwdParams bp, Grid gd)
 // ---------------------------------------------------------------------------
 // key pass
 // ---------------------------------------------------------------------------
-template <int D, bool BIDIR, int KMAX>
+// FAR: the dL/dy rows of a band lie too far apart for 32-bit offsets.
+template <int D, bool BIDIR, int KMAX, bool FAR>
 __global__ __launch_bounds__(NT) void smallk_bwd_kv_kernel(BwdParams bp, Grid gd) {
     using BD = Band<D, BIDIR, KMAX>;
     constexpr int E = BD::E, CPR = BD::CPR, ROWB = BD::ROWB;
@@ -246,7 +249,7 @@ __global__ __launch_bounds__(NT) void smallk_bwd_kv_kernel(BwdParams bp, Grid gd
     const int qlo = BIDIR ? j0 - kw : j0;
     const int lo = max(0, qlo);
     const int hi = (int)min((int64_t)j0 + TT + kw, (int64_t)N);
-    const int rowq_g = (int)(2 * p.sn), rowo_g = (int)(2 * bp.osn);
+    const int rowq_g = (int)(2 * p.sn), rowo_g = FAR ? 0 : (int)(2 * bp.osn);
     const int nw = BIDIR ? 2 * kw + 1 : kw + 1;
     // partner queries: j is the partner t - pi of t = j + pi, and (bidirectional)
     // the partner t + pi of t = j - pi
@@ -280,7 +283,12 @@ __global__ __launch_bounds__(NT) void smallk_bwd_kv_kernel(BwdParams bp, Grid gd
             const int offq = in ? (gr - lo) * rowq_g + 16 * c : kOutOfRange;
             const int offo = in ? (gr - lo) * rowo_g + 16 * c : kOutOfRange;
             nx.q[u] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rq, offq, 0, 0));
-            nx.o[u] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(ro, offo, 0, 0));
+            if constexpr (FAR) {
+                const uint4 o = *reinterpret_cast<const uint4 *>(op + min(max(gr, lo), hi - 1) * bp.osn + 8 * c);
+                nx.o[u] = in ? o : uint4{};
+            } else {
+                nx.o[u] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(ro, offo, 0, 0));
+            }
         }
         {   // per-row scalars of staged row tid (rows outside [lo, hi) read row lo)
             const int gr = qlo + tid;
@@ -414,7 +422,11 @@ hipError_t launch_kmax(const BwdParams &p, hipStream_t stream) {
     hipError_t e =
         launch_kernel(smallk_bwd_q_kernel<D, BIDIR, KMAX>, dim3((unsigned)grid), dim3(NT), stream, p, gd);
     if (e != hipSuccess) return e;
-    return launch_kernel(smallk_bwd_kv_kernel<D, BIDIR, KMAX>, dim3((unsigned)grid), dim3(NT), stream, p, gd);
+    const int64_t rows = std::min<int64_t>(p.f.N, TT + (BIDIR ? 2 : 1) * (int64_t)p.f.k);
+    const bool far = 2 * ((rows - 1) * p.osn + D) >= kOutOfRange;
+    return launch_kernel(
+        far ? smallk_bwd_kv_kernel<D, BIDIR, kSmallK, true> : smallk_bwd_kv_kernel<D, BIDIR, KMAX, false>,
+        dim3((unsigned)grid), dim3(NT), stream, p, gd);
 }
 
 template <int D, bool BIDIR>

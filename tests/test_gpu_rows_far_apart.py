@@ -1,5 +1,6 @@
-"""Rows so far apart that a tile's span more than 1 GiB: positions before the
-first row held still count as zeros, whatever lies in memory."""
+"""Rows so far apart that a tile's span more than 1 GiB, or 2: positions before
+the first row held still count as zeros, whatever lies in memory, and offsets
+are right."""
 import pytest
 import torch
 
@@ -28,3 +29,23 @@ def test_key_shard(device):
     call = lambda d: pa.pi_attn_backward_shard_kv(q, kk, v, gate, k, pi, N, kpos0, qpos0, lse, rt, d, causal=False)
     for a, b in zip(call(far), call(far.contiguous())):
         assert torch.isfinite(b[:, :, :64]).all() and torch.equal(a[:, :, :64], b[:, :, :64])
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("causal,k", [(True, 16), (False, 13), (False, 3)])
+def test_small_window_backward(device, D, causal, k):
+    """dL/dy and y rows that span 2 GiB per band of the small-window key pass:
+    the gradients of the same rows side by side, to the bit."""
+    H, N, pi = 2, 75, 20
+    step = (1 << 30) // (31 + (1 if causal else 2) * k) // 128 * 128 + 128   # the band's rows: 32 + k or 32 + 2k
+    cfg = W.ForwardConfig("custom", 1, H, N, D, k, pi, torch.bfloat16)
+    q, kk, v, gate = W.forward_inputs(cfg, 73, device, per_query_gate=True)
+    do = W.cotangent(q.shape, q.dtype, 73, device)
+    y, lse = pa.pi_attn_forward(q, kk, v, gate, k, pi, return_lse=True, causal=causal)
+    apart = [torch.empty(((N - 1) * step + H * D,), dtype=torch.bfloat16, device="cuda").as_strided(
+        (1, H, N, D), (0, D, step, 1)) for _ in range(2)]
+    apart[0].copy_(y)
+    apart[1].copy_(do)
+    got = pa.pi_attn_backward(q, kk, v, gate, k, pi, apart[0], lse, apart[1], causal=causal)
+    for a, b in zip(got, pa.pi_attn_backward(q, kk, v, gate, k, pi, y, lse, do, causal=causal)):
+        assert torch.equal(a, b)
