@@ -66,17 +66,20 @@ __device__ inline void load_cols(ColFrag<D> &f, RowPtr row, int c, int g) {
 }
 
 // Scores of the block's 16 rows with the tile's 16 columns: slot r of lane
-// (c, g) is <row 4 g + r, column c>.  Every 32 dims in four chains of two
-// instructions (their latency is longer than their issue), then a tree: the
-// fewer summands round one after the other, the smaller the error.  Relative
-// error of dk over fourteen problems of k = 8 to 128, D = 64 and 128: with a
-// tree over 64 lanes 3.10e-7 and 3.06e-7, four chains over all dims 3.07e-7 and
-// 3.18e-7, this 2.99e-7 and 2.92e-7; out, lse, dq and dv err less than with
-// either.  Against the chains over all dims: a backward at B4 H16 N4096 D64
-// k128 569 -> 545 us, B2 H16 N8192 D128 k256 1918 -> 1981 us, forwards equal.
+// (c, g) is <row 4 g + r, column c>.  In chains (an instruction's latency is
+// longer than its issue), four of two instructions for every 32 dims at D = 64,
+// four of four for every 64 at D = 128, then a tree: the fewer summands round
+// one after the other, the smaller the error.  Relative error of dk over
+// fourteen problems of k = 8 to 128, D = 64 and 128: with a tree over 64 lanes
+// 3.11e-7 and 3.06e-7, four chains over all dims 3.07e-7 and 3.18e-7, this
+// 2.99e-7 and 2.97e-7 (chains of two at D = 128 2.92e-7); out, lse, dq and dv
+// err less than with either.  us, a backward with four chains over all dims,
+// chains of two and of four: B4 H16 N4096 D64 k128 572, 547, -; B2 H16 N8192
+// D128 k256 1918, 1977, 1939; B4 H8 N300 D128 k300 127, 137, 131; forwards at
+// D = 128 526, 516, 519 and 44.4, 46.4, 44.9.
 template <int D, int S0, int N>
 __device__ inline f32x4 dot_range(const RowFrag<D> &rows, const RowFrag<D> &cols) {
-    if constexpr (N > 2) {
+    if constexpr (N > D / 32) {
         const f32x4 lo = dot_range<D, S0, N / 2>(rows, cols);
         return lo + dot_range<D, S0 + N / 2, N / 2>(rows, cols);
     } else {
