@@ -197,15 +197,23 @@ dim3 grid_of(const FwdParams &p) { return dim3((unsigned)(((int64_t)p.B * p.H * 
 
 }  // namespace
 
-// Which launches take these kernels.  A wavefront here costs so much per entry
-// of its row, a tile's so much per block of its columns' working sets and
-// something once: so many entries per tile are worth a block.  Both directions
-// take the same way: a score then errs alike in the lse and in the weights made
-// from it, and most of that cancels (otherwise dv errs 1.1 to 1.5 times as much).
-// Where the lines lie is measured over B H = 1 to 8192, N = 1 to 2048 and k = 0
-// to 24, causal and bidirectional, with and without partners (892 launches
-// each way); beside a line a forward loses up to 20 % for the backward's gain
-// or the other way round.  us, rows and tiles, D = 64 causal unless given:
+// Which launches take these kernels: by estimates of a forward and a backward
+// together, in units of about an entry's time where the chip is full (0.14 ns
+// at D = 64, 0.08 at D = 128, less a common part).  Here a row's own chain, or
+// all entries (at D = 64 also the rows).  In tiles, rounds of as many tiles as
+// run at once (a wavefront per SIMD, or four per tile), each as long as the
+// blocks of a tile's working sets.
+//
+// Both directions take the same way: a score then errs alike in the lse and in
+// the weights made from it, and most of that cancels (otherwise dv errs 1.1 to
+// 1.5 times as much).
+//
+// Measured with B H = 1 to 8192, N = 1 to 2048 and k = 0 to 24, causal and
+// bidirectional, with and without partners (1602 pairs of launches): the two
+// together take at most 1.15 (D = 64) and 1.26 (D = 128) times the shorter way,
+// by more than 10 % in 32; a forward alone takes up to 1.05 and 1.33 times as
+// long as in tiles where the backward gains more.  us, rows and tiles, D = 64
+// causal unless given:
 //   forward   B2 H8 N256 k1 4.5, 5.4;  k6 with partners 6.4, 5.5;
 //             B1024 H8 N1 k0 5.5, 12.5;  B128 H8 N33 k0 14.5, 9.3
 //   backward  B2 H8 N256 k1 9.7, 11.6;  k6 with partners 16.7, 12.1;
@@ -215,16 +223,19 @@ dim3 grid_of(const FwdParams &p) { return dim3((unsigned)(((int64_t)p.B * p.H * 
 //             162, 264;  k12 with partners 167, 81 and 513, 310
 bool one_per_row(const FwdParams &p) {
     const int64_t n = p.N, k = std::min<int64_t>(p.k, n - 1), sides = p.causal ? 1 : 2;
-    const int64_t rows = p.B * (int64_t)p.H * n, per_head = (n + 15) / 16, tiles = p.B * (int64_t)p.H * per_head;
+    const int64_t heads = p.B * (int64_t)p.H, rows = heads * n, tiles = f32::tiles_of(heads, p.N);
     if (rows * 64 + NT > (int64_t)UINT32_MAX) return false;   // the grid's threads must fit 32 bits
     const int64_t partners = partner_enabled(p.k, p.pi) ? std::max<int64_t>(0, n - p.pi) : 0;
-    const int64_t entries = n + sides * (n * k - k * (k + 1) / 2 + partners);   // of a head
+    const int64_t entries = n + sides * (n * k - k * (k + 1) / 2 + partners);                  // of a head
     const int64_t blocks = (std::min(n, 16 + sides * k) + 15) / 16 + (partners ? sides : 0);   // of a tile
-    const int64_t worth = tiles <= 256    ? (p.D == 64 ? 68 + 4 * blocks : 108 + 16 * blocks)   // a tile's latency
-                          : p.D == 64     ? 7 * blocks
-                          : tiles <= 1100 ? 24 + 28 * blocks   // about a tile per SIMD
-                                          : 4 + 18 * blocks;
-    return entries <= worth * per_head;
+    if (entries > 64 * n) return false;   // far past every line below
+    const bool split = tiles <= f32::kSplitTiles;
+    const int64_t rounds = split ? (tiles + 255) / 256 : (tiles + 1023) / 1024;
+    if (p.D == 64)
+        return std::max(3800 * entries / n, 5 * rows / 2 + heads * entries) <=
+               (split ? 8500 + rounds * (8700 + 3100 * blocks) : 8000 + rounds * (3700 + 12750 * blocks));
+    return std::max(2000 * entries / n, heads * entries) <=
+           (split ? 1000 + rounds * (7000 + 5100 * blocks) : rounds * (3100 + 17200 * blocks) + 7 * rows / 4);
 }
 
 hipError_t launch_forward_rows_f32(const FwdParams &p, hipStream_t stream) {

@@ -15,11 +15,14 @@ from tests.test_gpu_parity import LSE_TOL, assert_close, np32
 
 pytestmark = pytest.mark.gpu
 
-# (B, H, N, D, k, pi); tiles per launch <= 256, <= 1100 and above
+# (B, H, N, D, k, pi): launches of up to 512 tiles (split over four wavefronts
+# each) and of more, in one round and in two; most take rows causally and some
+# tiles bidirectionally
 SHAPES = [(1, 1, 1, 64, 0, 0), (2, 1, 2, 128, 1, 1), (1, 3, 5, 64, 2, 4), (1, 2, 16, 128, 7, 8), (1, 2, 17, 64, 2, 4),
-          (1, 2, 130, 64, 6, 16), (1, 2, 130, 64, 7, 16), (1, 2, 130, 128, 8, 9), (1, 2, 130, 128, 9, 10),
-          (1, 27, 150, 64, 1, 2), (1, 27, 150, 128, 3, 6), (1, 27, 150, 128, 6, 0), (2, 601, 1, 64, 0, 0),
-          (2, 601, 3, 128, 2, 4), (1, 601, 18, 64, 0, 1), (1, 601, 18, 128, 1, 2), (1, 601, 18, 128, 5, 6)]
+          (1, 2, 130, 64, 5, 16), (1, 2, 130, 64, 6, 16), (1, 2, 130, 128, 9, 10), (1, 2, 130, 128, 12, 13),
+          (1, 27, 150, 64, 4, 6), (1, 27, 150, 128, 7, 9), (2, 601, 1, 64, 0, 0), (1, 601, 18, 64, 2, 4),
+          (1, 601, 18, 64, 6, 8), (1, 601, 18, 128, 1, 2), (1, 601, 18, 128, 10, 12), (1, 1040, 5, 64, 3, 4),
+          (1, 1040, 12, 128, 8, 10)]
 
 
 @pytest.mark.parametrize("B,H,N,D,k,pi", SHAPES)
