@@ -268,13 +268,15 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void forward_bf16_kernel(FwdPa
     // ---- prologue: every load is issued before any is waited for ----------
     // (the query fragments, the gate logit, the partner key/value rows, then
     // the first tile), so the prologue costs one memory round trip.  Causal at
-    // D = 128 the tile goes before the partners: the compiler moves one of
-    // their registers as soon as it is loaded, and a tile fetched after them
-    // waited a round trip for that (68.2 -> 60.5 us at B256 H16 N64 k17, 29.0
-    // -> 28.1 us at B64 H16 N128 k32, equal at N32768); bidirectionally, with
-    // the second partner behind the first, it gains nothing (763 -> 773 us at
-    // B1 H32 N32768 k512).
-    constexpr bool TILE_FIRST = D == 128 && !BIDIR;
+    // D = 128 the compiler moves one of the partners' registers as soon as it is
+    // loaded, and the tile's fetch behind them waits a round trip for that.
+    // Where a sequence is one query tile, the tile goes before them (45.9 ->
+    // 40.6 us at B256 H16 N20 k17, 30.2 -> 29.4 at B64 H16 N128 k32).  Where
+    // other tiles' work-groups read the same rows, it stays behind: the partner
+    // rows then come from the L2 more often (68.5 and 71.2 us at B4 H16 N4096
+    // k128 in [B][N][H][D] storage; bidirectionally, B1 H32 N32768 k512, 763
+    // and 773).
+    const bool tile_first = D == 128 && !BIDIR && n_qt == 1;
     // Buffer descriptors over rows [kb0, kend) of this head's keys and values,
     // up to the last row's end (row strides may be below D, or 0).
     const int rowb = (int)(2 * ksn);
@@ -310,7 +312,7 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void forward_bf16_kernel(FwdPa
     }
     const float gl = p.gate[b * p.gsb + h * p.gsh + (tq - p.qpos0) * p.gsn];
 
-    if (TILE_FIRST && ntiles > 0) tile_fetch<D>(tA, rk, rv, rowb, 0, w, lane);
+    if (tile_first && ntiles > 0) tile_fetch<D>(tA, rk, rv, rowb, 0, w, lane);
 
     // Partner rows: A-operand row c of the wavefront is row q0 + c - pi, the
     // partner of query q0 + c; the accumulator seed is that row's value, of
@@ -342,7 +344,7 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void forward_bf16_kernel(FwdPa
             vff[s] = *reinterpret_cast<const bf16x8 *>(vp + frc * ksn + 16 * s + 8 * g);
         }
     }
-    if (!TILE_FIRST && ntiles > 0) tile_fetch<D>(tA, rk, rv, rowb, 0, w, lane);
+    if (!tile_first && ntiles > 0) tile_fetch<D>(tA, rk, rv, rowb, 0, w, lane);
     if constexpr (QLDS) {
         __builtin_amdgcn_s_waitcnt(0xF70);   // vmcnt(0): this wavefront's own fetches, read by itself alone
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
