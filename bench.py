@@ -521,7 +521,7 @@ def main():
                   "us_per_step_p50": round(per[len(per) // 2] * 1e3, 2),
                   "us_per_step_p99": round(per[min(len(per) - 1, (99 * len(per)) // 100)] * 1e3, 2),
                   "queries_per_s": round(dcfg.S / (dms / 1e3), 1),
-                  "roofline": {"bound": "hbm", "kernel": "decode_kernel<bf16,128,false,8,8,true>",
+                  "roofline": {"bound": "hbm", "kernel": "decode_kernel<bf16,128,false,8,8,true,true>",
                                "achieved": round(dgbs, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                "frac": round(dgbs / HBM_PEAK_GBS, 4), "bytes_per_step": dbytes,
                                "traffic": dtraffic, **dcounters}}

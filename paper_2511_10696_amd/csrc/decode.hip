@@ -80,8 +80,9 @@ __device__ inline float row_sum(float x) {
     return x;
 }
 
-// CH: load instructions per chunk; ONCE: window rows are not kept in the caches.
-template <typename T, int D, bool CLAMP, int WAVES, int CH, bool ONCE>
+// CH: load instructions per chunk; ONCE: window rows are not kept in the caches;
+// PACED: with few of a wavefront's loads in flight at a time.
+template <typename T, int D, bool CLAMP, int WAVES, int CH, bool ONCE, bool PACED>
 __global__ __launch_bounds__(64 * WAVES) void decode_kernel(DecodeParams p) {
     using R = Row<T, D>;
     constexpr int LPR = R::LPR, RPI = R::RPI, EPL = R::EPL;
@@ -124,13 +125,22 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kernel(DecodeParams p) {
 
     uint4 kr[CH], vr[CH];
     // Slots past the window read its last row again (and count as zeros below):
-    // behind a branch each, every load was waited for before the next.
+    // behind a branch each, every load is waited for before the next few, which
+    // is what PACED is for.
     auto load = [&](int ch) __attribute__((always_inline)) {
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-            const int64_t off = (int64_t)(lo + min(ch * RPC + c * RPI + rg, nwin - 1)) * D;
-            kr[c] = ONCE ? ld16_once(kc + off) : ld16(kc + off);
-            vr[c] = ONCE ? ld16_once(vc + off) : ld16(vc + off);
+            const int i = ch * RPC + c * RPI + rg;
+            if constexpr (PACED) {
+                const bool in = i < nwin;
+                const int64_t off = (int64_t)(lo + i) * D;
+                kr[c] = in ? ld16_once(kc + off) : make_uint4(0, 0, 0, 0);
+                vr[c] = in ? ld16_once(vc + off) : make_uint4(0, 0, 0, 0);
+            } else {
+                const int64_t off = (int64_t)(lo + min(i, nwin - 1)) * D;
+                kr[c] = ONCE ? ld16_once(kc + off) : ld16(kc + off);
+                vr[c] = ONCE ? ld16_once(vc + off) : ld16(vc + off);
+            }
         }
     };
     // logit (log2 units) of a row from this lane's part of it
@@ -199,7 +209,7 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kernel(DecodeParams p) {
         l *= alpha;
 #pragma unroll
         for (int e = 0; e < EPL; ++e) acc[e] *= alpha;
-        if ((ch + 1) * RPC > nwin) {
+        if (!PACED && (ch + 1) * RPC > nwin) {
 #pragma unroll
             for (int c = 0; c < CH; ++c)
                 if (ch * RPC + c * RPI + rg >= nwin) vr[c] = make_uint4(0, 0, 0, 0);
@@ -261,11 +271,12 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kernel(DecodeParams p) {
 // 64, k = 384, 3 MB), and from 17 MB on the other way round.
 constexpr int64_t kKeepBytes = 12 << 20;
 
-template <typename T, int D, bool CLAMP, int WAVES, int CH>
+template <typename T, int D, bool CLAMP, int WAVES, int CH, bool PACED = false>
 hipError_t launch_n(const DecodeParams &p, hipStream_t stream) {
     const int64_t n = (int64_t)p.S * p.H;
     const bool once = 2 * n * std::min(p.k, p.cap) * D * (int64_t)sizeof(T) > kKeepBytes;
-    return launch_kernel(once ? decode_kernel<T, D, CLAMP, WAVES, CH, true> : decode_kernel<T, D, CLAMP, WAVES, CH, false>,
+    return launch_kernel(once ? decode_kernel<T, D, CLAMP, WAVES, CH, true, PACED>
+                              : decode_kernel<T, D, CLAMP, WAVES, CH, false, false>,
                          dim3((unsigned)n), dim3(64 * WAVES), stream, p);
 }
 
@@ -277,15 +288,25 @@ hipError_t launch_n(const DecodeParams &p, hipStream_t stream) {
 // 2.1 to 3 times as fast from 4096 (s, h) on, float32 D = 64, k = 4 at 8192:
 // 22 -> 9.4 us; 3 to 8: 1.2 to 1.8 times), a few (s, h) by one wavefront's
 // chain (9 to 32 loads at 32 and 256 (s, h): equal to 12% faster), and eight
-// wavefronts of eight slots stream long windows best from 33 loads on (1 to 3%
-// at 4096 (s, h), 12% at 32 and 128 loads; below, up to 1.7 times as long).
+// wavefronts stream long windows best from 33 loads on (1 to 3% at 4096 (s, h),
+// 12% at 32 and 128 loads; below, up to 1.7 times as long).  Of four slots:
+// bf16 D = 128 k = 512 at 2048 (s, h) 80.3 to 84 us by the caches' capacity, of
+// eight 82.0 to 85, D = 64 k = 300 26.0 and 27.9, 32 (s, h) 6.3 and 6.5;
+// float32 D = 128 k = 512 at 2048 the other way round, 164.7 and 163.3.  Where
+// long windows are 400 MB and more together (a load instruction is 1 KiB), the
+// memory is a little faster when each wavefront has few loads in flight: D =
+// 128, k = 512 at 2048 (s, h) 80.5 and 82.2 us, k = 1024 161.6 and 164.3,
+// float32 D = 64, k = 512 81.0 and 83.5.  With 268 MB it is the other way round
+// (42.9 and 41.2 us, D = 64 42.7 and 41.1), and so with 68 loads, little more
+// than a chunk for each wavefront (99.5 and 90.6 us at 4096 (s, h), k = 270).
 // A launch has fewer than 2^32 threads: from 2^24 (s, h) on, one wavefront.
 template <typename T, int D, bool CLAMP>
 hipError_t launch_w(const DecodeParams &p, hipStream_t stream) {
     const int64_t n = (int64_t)p.S * p.H;
     const int loads = (std::min(p.k, p.cap) + Row<T, D>::RPI - 1) / Row<T, D>::RPI;
     if (n >= (1 << 24)) return launch_n<T, D, CLAMP, 1, 2>(p, stream);
-    if (loads > 32) return launch_n<T, D, CLAMP, 8, 8>(p, stream);
+    if (loads >= 128 && 2 * n * loads > (400 << 10)) return launch_n<T, D, CLAMP, 8, 8, true>(p, stream);
+    if (loads > 32) return launch_n<T, D, CLAMP, 8, 4>(p, stream);
     if (loads > 8 || (loads > 4 && n <= 1024)) return launch_n<T, D, CLAMP, 4, 4>(p, stream);
     if (loads > 2 || n < 2048) return launch_n<T, D, CLAMP, 2, 2>(p, stream);
     return launch_n<T, D, CLAMP, 1, 2>(p, stream);

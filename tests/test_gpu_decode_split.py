@@ -115,3 +115,24 @@ def test_partner_of_weight_zero(device, dtype):
     assert torch.isnan(out[..., 5]).all()
     out[..., 5] = 0
     assert torch.isfinite(out).all()
+
+
+@pytest.mark.parametrize("dtype,D,k", [(torch.bfloat16, 128, 517), (torch.float32, 64, 513)])
+def test_decode_paced(device, dtype, D, k):
+    """A step of more than 400 MB of window rows: three of its sequences, one
+    shorter than a chunk, against the oracle."""
+    S, H, pi, cap = 64, 32, k + 3, k + 20
+    g = torch.Generator(device="cuda").manual_seed(37)
+    kc, vc = (torch.randn(S, H, cap, D, generator=g, device="cuda", dtype=dtype) for _ in range(2))
+    qn, kn, vn = (torch.randn(S, H, D, generator=g, device="cuda", dtype=dtype) for _ in range(3))
+    gate = torch.rand(H, generator=g, device="cuda") * 2 - 1
+    lens = torch.full((S,), cap - 1, device="cuda", dtype=torch.int32)
+    lens[5], lens[63] = 3, k
+    pick = [0, 5, 63]
+    for s in pick:   # rows past the length are never read
+        kc[s, :, lens[s]:], vc[s, :, lens[s]:] = float("nan"), float("nan")
+    kc_ref, vc_ref = np32(kc[pick]), np32(vc[pick])
+    out = pa.pi_attn_decode_step(lens, qn, kn, vn, kc, vc, gate, k, pi)
+    ref = oracle.decode_step(lens[pick].cpu().numpy(), qn[pick], kn[pick], vn[pick], kc_ref, vc_ref, gate, k, pi)
+    assert_close(np32(out[pick]), ref, dtype)
+    assert torch.isfinite(out).all()
